@@ -191,44 +191,40 @@ rsr_status check_consistency(rsr_ctx* ctx, rsr_refs* refs, const std::vector<uin
 
 // Byte offsets of a model's device arrays in its single allocation (and in
 // its pinned staging buffer): thresholds u64 [n][K-1], probabilities f64
-// [n][K], sampler threshold halves i32 [ceil(n/8)*8][K-1][2], probabilities
-// f32 [n][K].  Every offset is a multiple of 8.
+// [n][K], sampler thresholds u32 [PW][K-1][kPackWords], probabilities f32
+// [n][K].  Every offset is a multiple of 8.
 struct ModelLayout {
-    size_t thresh, p64, half, p32, total;
+    size_t thresh, p64, pack, p32, total;
     ModelLayout(int n, int K) {
         const size_t nn = static_cast<size_t>(n), k1 = static_cast<size_t>(K - 1);
-        const size_t n_pad = (nn + 7) / 8 * 8;
         thresh = 0;
         p64 = thresh + sizeof(uint64_t) * nn * k1;
-        half = p64 + sizeof(double) * nn * K;
-        p32 = half + sizeof(int32_t) * n_pad * k1 * 2;
+        pack = p64 + sizeof(double) * nn * K;
+        p32 = pack + sizeof(uint32_t) * plane_words(n) * k1 * rsr::kPackWords;
         total = p32 + sizeof(float) * nn * K;
     }
 };
 
-// The host images of a model's arrays (p already validated).  The sampler
-// form of a threshold C is a pair (gt, eq) on the high 16 bits of a uniform
-// word u: u >= C is true when (u >> 16) > gt and needs the low half only when
-// (u >> 16) == eq; padding components never set a bit.
+// The host images of a model's arrays (p already validated).  Padding
+// components of the sampler form never set a bit.
 void fill_model_stage(const ModelLayout& L, int n, int K, const double* p, void* stage) {
     char* base = static_cast<char*>(stage);
     uint64_t* C = reinterpret_cast<uint64_t*>(base + L.thresh);
     compute_thresholds(n, K, p, C);
     std::memcpy(base + L.p64, p, sizeof(double) * static_cast<size_t>(n) * K);
-    int32_t* half = reinterpret_cast<int32_t*>(base + L.half);
-    const size_t n_pad = (static_cast<size_t>(n) + 7) / 8 * 8;
-    for (size_t i = 0; i < n_pad; ++i)
+    uint32_t* pack = reinterpret_cast<uint32_t*>(base + L.pack);
+    for (int wi = 0; wi < plane_words(n); ++wi)
         for (int s = 0; s < K - 1; ++s) {
-            int32_t gt = 0x7FFFFFFF, eq = -1;
-            if (i < static_cast<size_t>(n)) {
-                const uint64_t c = C[i * (K - 1) + s];
-                const int32_t ch = static_cast<int32_t>(c >> 16);
-                const bool low_zero = (c & 0xFFFFu) == 0;
-                gt = low_zero ? ch - 1 : ch;
-                eq = low_zero ? -1 : ch;
+            uint32_t* pw = pack + (static_cast<size_t>(wi) * (K - 1) + s) * rsr::kPackWords;
+            std::fill(pw, pw + rsr::kPackWords, 0u);
+            for (int k = 0; k < 32; ++k) {
+                const int i = 32 * wi + k;
+                const rsr::PackedThreshold t = rsr::pack_threshold(
+                    i < n ? C[static_cast<size_t>(i) * (K - 1) + s] : uint64_t{1} << 32);
+                pw[k / 2] |= static_cast<uint32_t>(t.s) << (16 * (k % 2));
+                if (t.always) pw[16] |= 1u << k;
+                if (t.force) pw[17] = 1u;
             }
-            half[(i * (K - 1) + s) * 2] = gt;
-            half[(i * (K - 1) + s) * 2 + 1] = eq;
         }
     float* pf = reinterpret_cast<float*>(base + L.p32);
     for (size_t i = 0; i < static_cast<size_t>(n) * K; ++i) pf[i] = static_cast<float>(p[i]);
@@ -386,7 +382,7 @@ rsr_status rsr_model_create(rsr_ctx* ctx, int32_t n, int32_t K, const double* p,
     char* base = static_cast<char*>(m->d_mem);
     m->d_thresh = reinterpret_cast<uint64_t*>(base + L.thresh);
     m->d_p64 = reinterpret_cast<double*>(base + L.p64);
-    m->d_half = reinterpret_cast<int32_t*>(base + L.half);
+    m->d_pack = reinterpret_cast<uint32_t*>(base + L.pack);
     m->d_p = reinterpret_cast<float*>(base + L.p32);
     fill_model_stage(L, n, K, p, m->h_stage);
     e = hipMemcpyAsync(m->d_mem, m->h_stage, L.total, hipMemcpyHostToDevice, ctx->stream);
@@ -757,7 +753,8 @@ rsr_status rsr_sample(rsr_ctx* ctx, const rsr_model* model, uint64_t seed, uint3
     if (!model || !d_samples) return fail(ctx, RSR_EINVAL, "NULL model or d_samples");
     if (N <= 0) return fail(ctx, RSR_EINVAL, "N must be > 0");
     DeviceGuard g(ctx->device);
-    RSR_HIP(ctx, rsr::launch_sample(ctx->stream, model, seed, stream_id, first_sample, N, d_samples));
+    RSR_HIP(ctx, rsr::launch_sample(ctx->stream, model, seed, stream_id, first_sample, N,
+                                    ctx->cu_count, d_samples));
     return RSR_OK;
 }
 

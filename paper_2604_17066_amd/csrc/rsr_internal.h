@@ -25,6 +25,32 @@ constexpr int kMaxGradBlocks = 64;
 constexpr int kMaxMfmaSteps = 20;   // int8 form: 64 k per step, 1280 bits
 constexpr int kMaxMfma4Steps = 10;  // FP4 form: 128 k per step, 1280 bits
 
+// Sampler form of the thresholds of one packed word (32 components) and one
+// plane: 16 dwords of 16-bit thresholds (dword 4 q + j holds components 8 q +
+// 2 j in its low and 8 q + 2 j + 1 in its high half, the halves' positions in
+// Philox block q), the word's always-up components as a bit mask, and a flag
+// (nonzero: no component of the word may be decided from its high half).
+constexpr int kPackWords = 18;
+
+// The 16-bit threshold s of a threshold C in [0, 2^32], such that for the high
+// half u of a uniform word min(max(u - s, 0), 2) is 0 when the word is below
+// C, 2 when it is not, and 1 when the low half has to decide (or, harmlessly,
+// where it would not have to: that path compares the whole word).
+struct PackedThreshold {
+    uint16_t s;
+    bool always, force;
+};
+inline PackedThreshold pack_threshold(uint64_t C) {
+    const uint32_t high = static_cast<uint32_t>(C >> 16);
+    if (C == 0) return {65535, true, false};               // every word is at or above 0
+    if (high >= 65536) return {65535, false, false};       // none is at or above 2^32
+    if ((C & 0xFFFFu) == 0)                                // decided: u >= high
+        return high >= 2 ? PackedThreshold{static_cast<uint16_t>(high - 2), false, false}
+                         : PackedThreshold{65535, false, true};
+    return high >= 1 ? PackedThreshold{static_cast<uint16_t>(high - 1), false, false}
+                     : PackedThreshold{65535, false, true};
+}
+
 // Every device and pinned-host allocation of the library goes through these
 // two, so that rsr_debug_fail_alloc can make a chosen one fail.
 hipError_t dev_malloc(void** p, size_t bytes);
@@ -93,11 +119,7 @@ struct rsr_model {
     hipEvent_t staged = nullptr;   // recorded after the last staged upload
     uint64_t* d_thresh = nullptr;  // [n][K-1]
     double* d_p64 = nullptr;       // [n][K] the probabilities as given
-    // Sampler form of the thresholds, [ceil(n/8)*8][K-1] pairs (gt, eq) of
-    // int32 on the high 16 bits of the uniform word u: u >= C is decided true
-    // by (u >> 16) > gt, and needs the low half only when (u >> 16) == eq.
-    // Padding components never set a bit (gt = INT32_MAX, eq = -1).
-    int32_t* d_half = nullptr;
+    uint32_t* d_pack = nullptr;    // [PW][K-1][kPackWords], see pack_threshold
     float* d_p = nullptr;          // [n][K] fp32 copy of the probabilities
 };
 
@@ -143,7 +165,7 @@ namespace rsr {
 // Device-side record of one job of a batched plan.
 struct JobDev {
     const uint64_t* thresh;  // [n][K-1]
-    const int32_t* half;     // rsr_model::d_half
+    const uint32_t* pack;    // rsr_model::d_pack
     const float* p;          // [n][K]
     uint32_t* samples;       // [W][N]
     uint8_t* flags;          // [N]
@@ -292,7 +314,7 @@ constexpr int kMaxHeadSteps = 10;
 
 // Kernel launchers (each returns the hipError_t of the launch).
 hipError_t launch_sample(hipStream_t st, const rsr_model* m, uint64_t seed, uint32_t stream_id,
-                         uint64_t first, int64_t N, uint32_t* d_samples);
+                         uint64_t first, int64_t N, int cus, uint32_t* d_samples);
 hipError_t launch_dom_bits(hipStream_t st, const rsr_refs* refs, const uint32_t* d_samples,
                            int64_t N, int mode, uint8_t* d_flags, uint32_t* d_match);
 hipError_t launch_dom_cascade(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
