@@ -227,8 +227,10 @@ rsr_status rsr_sample(rsr_ctx* ctx, const rsr_model* model, uint64_t seed, uint3
  * ALU), RSR_MFMA (int8 matrix-core contraction of eq. violation_matrix, COUNT
  * and LABEL modes alike), RSR_MFMA_FP4 (the same contraction with FP4 E2M1
  * operands 0 / +-1 and fp32 accumulation, exact because every partial sum
- * is a small integer), RSR_AUTO (the cascade for LABEL mode on consistent
- * rows, else the FP4 form up to 1280 bits, else the popcount form),
+ * is a small integer), RSR_AUTO (for LABEL mode on consistent rows the
+ * sparse form, which tests only the components that a row constrains, or the
+ * cascade where the rows constrain most of them; else the FP4 form up to
+ * 1280 bits, else the popcount form),
  * RSR_PERSIST (the cascade with its rounds after round 0 in one persistent,
  * cooperative launch; its grid barriers wait with a time limit, and a
  * barrier that timed out is reported as RSR_EHIP by the next rsr_estimate).
@@ -403,7 +405,7 @@ typedef struct {
  *                     consistency, matrix-core operands, jobs and samples per
  *                     job) and whose values are the chosen configuration:
  *                     {"choice": 0 cascade, 1 popcount per job, 2 int8
- *                     per job, 3 FP4 per job, 4 persistent cascade;
+ *                     per job, 3 FP4 per job, 4 persistent cascade, 5 sparse;
  *                     "first", "growth", "split": the cascade's round
  *                     rows; "tail": 0 popcount rounds, 1 FP4 rounds after
  *                     round 0, 2 FP4 rounds from round 0 on; "chunks"

@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -430,8 +431,9 @@ rsr_status rsr_model_destroy(rsr_model* m) {
 
 namespace rsr {
 
-rsr_status refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
-                       const uint8_t* upper, int64_t R_U, bool matrix_operands, rsr_refs** out) {
+static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
+                             const uint8_t* upper, int64_t R_U, bool matrix_operands,
+                             rsr_refs** out) {
     if (!ctx || !out) return RSR_EINVAL;
     *out = nullptr;
     if (n <= 0 || K < 2) return fail(ctx, RSR_EINVAL, "n must be > 0 and K >= 2");
@@ -440,53 +442,81 @@ rsr_status refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower,
     if (R_L < 0 || R_U < 0) return fail(ctx, RSR_EINVAL, "negative row count");
     if ((R_L > 0 && !lower) || (R_U > 0 && !upper))
         return fail(ctx, RSR_EINVAL, "NULL reference rows with a non-zero count");
-    for (int64_t k = 0; k < R_L * n; ++k)
-        if (lower[k] >= K) return fail(ctx, RSR_EINVAL, "lower reference state >= K");
-    for (int64_t k = 0; k < R_U * n; ++k)
-        if (upper[k] >= K) return fail(ctx, RSR_EINVAL, "upper reference state >= K");
-    DeviceGuard g(ctx->device);
     const int PW = plane_words(n);
     const int W = sample_words(n, K);
     const int WR = rsr::dom_row_words(W);
-    if (WR < 0) return fail(ctx, RSR_EUNSUPPORTED, "packed width not supported");
     // Valid-bit mask per packed word (pad bits of each plane are 0).
     std::vector<uint32_t> valid(W, 0u);
     for (int j = 1; j < K; ++j)
         for (int i = 0; i < n; ++i) valid[(j - 1) * PW + i / 32] |= 1u << (i % 32);
-    auto pack = [&](const uint8_t* row, uint32_t* dst, bool complement) {
-        for (int w = 0; w < WR; ++w) dst[w] = 0u;
-        for (int j = 1; j < K; ++j)
-            for (int i = 0; i < n; ++i)
-                if (row[i] >= j) dst[(j - 1) * PW + i / 32] |= 1u << (i % 32);
-        if (complement)
-            for (int w = 0; w < W; ++w) dst[w] = ~dst[w] & valid[w];
+    // Packs rows (complemented or not) into thermometer words, eight
+    // components at a time: adding 128 - j to a byte sets its top bit when the
+    // state is at least j (states are below 128), and a product gathers the
+    // eight top bits.  False on a state >= K.
+    auto pack = [&](const uint8_t* rows, int64_t R, bool complement, std::vector<uint32_t>& out) {
+        constexpr uint64_t kOnes = 0x0101010101010101ull, kTop = 0x8080808080808080ull;
+        for (int64_t r = 0; r < R; ++r) {
+            const uint8_t* row = rows + r * n;
+            uint32_t* dst = out.data() + r * WR;
+            for (int i = 0; i < n; i += 8) {
+                uint64_t x = 0;
+                std::memcpy(&x, row + i, static_cast<size_t>(std::min(8, n - i)));
+                if ((x | (x + kOnes * static_cast<uint64_t>(128 - K))) & kTop) return false;
+                for (int j = 1; j < K; ++j) {
+                    const uint64_t ge = ((x + kOnes * static_cast<uint64_t>(128 - j)) & kTop) >> 7;
+                    dst[(j - 1) * PW + i / 32] |=
+                        static_cast<uint32_t>((ge * 0x0102040810204080ull) >> 56) << (i % 32);
+                }
+            }
+            if (complement)
+                for (int w = 0; w < W; ++w) dst[w] = ~dst[w] & valid[w];
+        }
+        return true;
     };
-    std::vector<uint32_t> lo(static_cast<size_t>(R_L) * WR), up(static_cast<size_t>(R_U) * WR);
-    for (int64_t r = 0; r < R_L; ++r) pack(lower + r * n, lo.data() + r * WR, true);
-    for (int64_t r = 0; r < R_U; ++r) pack(upper + r * n, up.data() + r * WR, false);
+    if (WR < 0) {
+        auto bad = [K](uint8_t v) { return v >= K; };
+        if (std::any_of(lower, lower + R_L * n, bad))
+            return fail(ctx, RSR_EINVAL, "lower reference state >= K");
+        if (std::any_of(upper, upper + R_U * n, bad))
+            return fail(ctx, RSR_EINVAL, "upper reference state >= K");
+        return fail(ctx, RSR_EUNSUPPORTED, "packed width not supported");
+    }
+    std::vector<uint32_t> lo(static_cast<size_t>(R_L) * WR, 0u), up(static_cast<size_t>(R_U) * WR, 0u);
+    if (!pack(lower, R_L, true, lo)) return fail(ctx, RSR_EINVAL, "lower reference state >= K");
+    if (!pack(upper, R_U, false, up)) return fail(ctx, RSR_EINVAL, "upper reference state >= K");
+    DeviceGuard g(ctx->device);
     // Store rows by increasing number of violation bits (stable): a row with
     // fewer constrained components dominates a larger region, so the LABEL
-    // cascade finds most matches among the first rows.  Results do not depend
+    // forms find most matches among the first rows.  Results do not depend
     // on the order.
-    auto sort_rows = [&](std::vector<uint32_t>& rows, int64_t R) {
+    auto sort_rows = [&](std::vector<uint32_t>& rows, int64_t R, std::vector<int>& weight) {
         std::vector<int64_t> order(R);
-        std::vector<int> weight(R);
+        std::vector<int> of(R);
         for (int64_t r = 0; r < R; ++r) {
             order[r] = r;
             int c = 0;
             for (int w = 0; w < W; ++w) c += __builtin_popcount(rows[r * WR + w]);
-            weight[r] = c;
+            of[r] = c;
         }
         std::stable_sort(order.begin(), order.end(),
-                         [&](int64_t a, int64_t b) { return weight[a] < weight[b]; });
+                         [&](int64_t a, int64_t b) { return of[a] < of[b]; });
         std::vector<uint32_t> sorted(rows.size());
-        for (int64_t r = 0; r < R; ++r)
+        weight.resize(R);
+        for (int64_t r = 0; r < R; ++r) {
             std::copy(rows.begin() + order[r] * WR, rows.begin() + (order[r] + 1) * WR,
                       sorted.begin() + r * WR);
+            weight[r] = of[order[r]];
+        }
         rows.swap(sorted);
     };
-    sort_rows(lo, R_L);
-    sort_rows(up, R_U);
+    std::vector<int> lo_weight, up_weight;
+    sort_rows(lo, R_L, lo_weight);
+    sort_rows(up, R_U, up_weight);
+    // f(k) for every set bit k of a packed row.
+    auto for_bits = [&](const uint32_t* row, auto f) {
+        for (int w = 0; w < W; ++w)
+            for (uint32_t m = row[w]; m; m &= m - 1) f(32 * w + __builtin_ctz(m));
+    };
 
     // Matrix-core operands: fragment-ordered bytes and accumulator starts,
     // chosen so that a row matches exactly when its accumulator is negative.
@@ -503,80 +533,93 @@ rsr_status refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower,
     std::vector<uint8_t> lof4, upf4, lof32, upf32;
     std::vector<float> loc4, upc4;
     if (with_mfma) {
-        auto frag = [&](const uint32_t* words, int64_t r, int8_t value, std::vector<int8_t>& dst) {
-            const int64_t T = r / 16;
-            const int rr = static_cast<int>(r % 16);
-            for (int k = 0; k < W * 32; ++k) {
-                if (!((words[k / 32] >> (k % 32)) & 1u)) continue;
-                const int s = k / 64, o = k % 64;
-                const int lane = (o / 16) * 16 + rr;
-                dst[((static_cast<size_t>(T) * KS + s) * 64 + lane) * 16 + (o % 16)] = value;
-            }
-        };
+        const int64_t TL32 = (R_L + 31) / 32, TU32 = (R_U + 31) / 32;
         lof.assign(static_cast<size_t>(TL) * KS * 1024, 0);
         upf.assign(static_cast<size_t>(TU) * KS * 1024, 0);
         loc.assign(static_cast<size_t>(TL) * 16, 0);
         upc.assign(static_cast<size_t>(TU) * 16, 0);
-        for (int64_t r = 0; r < R_L; ++r) {
-            frag(lo.data() + r * WR, r, 1, lof);
-            loc[r] = -1;
-        }
-        for (int64_t r = 0; r < R_U; ++r) {
-            frag(up.data() + r * WR, r, -1, upf);
-            int pop = 0;
-            for (int w = 0; w < W; ++w) pop += __builtin_popcount(up[r * WR + w]);
-            upc[r] = pop - 1;
-        }
-        // FP4 operands: 128 k per step; lane (group g, row rr) holds nibbles
-        // j = 0..31 for k = 128 s + 32 g + j, two per byte, low nibble first.
-        auto frag4 = [&](const uint32_t* words, int64_t r, uint8_t nib, std::vector<uint8_t>& dst) {
-            const int64_t T = r / 16;
-            const int rr = static_cast<int>(r % 16);
-            for (int k = 0; k < W * 32; ++k) {
-                if (!((words[k / 32] >> (k % 32)) & 1u)) continue;
-                const int s = k / 128, o = k % 128;
-                const int lane = (o / 32) * 16 + rr, j = o % 32;
-                dst[((static_cast<size_t>(T) * KS4 + s) * 64 + lane) * 16 + j / 2] |=
-                    static_cast<uint8_t>(nib << (4 * (j % 2)));
-            }
-        };
         lof4.assign(static_cast<size_t>(TL) * KS4 * 1024, 0);
         upf4.assign(static_cast<size_t>(TU) * KS4 * 1024, 0);
         loc4.assign(static_cast<size_t>(TL) * 16, 0.5f);
         upc4.assign(static_cast<size_t>(TU) * 16, 0.5f);
+        lof32.assign(static_cast<size_t>(TL32) * KS * 1024, 0);
+        upf32.assign(static_cast<size_t>(TU32) * KS * 1024, 0);
+        // int8: 64 k per step; lane (group g, row rr) holds k = 64 s + 16 g ..
+        // + 15.  FP4: 128 k per step; lane (group g, row rr) holds nibbles j =
+        // 0..31 for k = 128 s + 32 g + j, two per byte, low nibble first.  FP4
+        // on 32-row tiles: 64 k per step; lane (half h, row rr) holds nibbles j
+        // for k = 64 s + 32 h + j, +1 on both sides (the kernel starts every
+        // row at -1/2 and contracts upper rows with the complemented samples).
+        auto frags = [&](const uint32_t* row, int64_t r, int8_t value, uint8_t nib,
+                         std::vector<int8_t>& f8, std::vector<uint8_t>& f4,
+                         std::vector<uint8_t>& f32) {
+            int8_t* t8 = f8.data() + static_cast<size_t>(r / 16) * KS * 1024;
+            uint8_t* t4 = f4.data() + static_cast<size_t>(r / 16) * KS4 * 1024;
+            uint8_t* t32 = f32.data() + static_cast<size_t>(r / 32) * KS * 1024;
+            const int r16 = static_cast<int>(r % 16), r32 = static_cast<int>(r % 32);
+            for_bits(row, [&](int k) {
+                const int s = k / 64, o = k % 64, s4 = k / 128, o4 = k % 128, j = k % 32;
+                t8[(s * 64 + (o / 16) * 16 + r16) * 16 + o % 16] = value;
+                t4[(s4 * 64 + (o4 / 32) * 16 + r16) * 16 + j / 2] |=
+                    static_cast<uint8_t>(nib << (4 * (j % 2)));
+                t32[(s * 64 + (o / 32) * 32 + r32) * 16 + j / 2] |=
+                    static_cast<uint8_t>(0x2 << (4 * (j % 2)));
+            });
+        };
         for (int64_t r = 0; r < R_L; ++r) {
-            frag4(lo.data() + r * WR, r, 0x2, lof4);  // +1.0
+            frags(lo.data() + r * WR, r, 1, 0x2, lof, lof4, lof32);  // +1.0
+            loc[r] = -1;
             loc4[r] = -0.5f;
         }
         for (int64_t r = 0; r < R_U; ++r) {
-            frag4(up.data() + r * WR, r, 0xA, upf4);  // -1.0
+            frags(up.data() + r * WR, r, -1, 0xA, upf, upf4, upf32);  // -1.0
+            upc[r] = up_weight[r] - 1;
             upc4[r] = static_cast<float>(upc[r]) + 0.5f;  // |t(r)| - 0.5
         }
-        // FP4 operands on 32-row tiles: 64 k per step; lane (half h, row rr)
-        // holds nibbles j = 0..31 for k = 64 s + 32 h + j.  Both sides are +1
-        // nibbles (NOT t(r) for lower rows, t(r) for upper rows); the kernel
-        // starts every row at -1/2 and contracts upper rows with the
-        // complemented samples.
-        auto frag32 = [&](const uint32_t* words, int64_t r, std::vector<uint8_t>& dst) {
-            const int64_t T = r / 32;
-            const int rr = static_cast<int>(r % 32);
-            for (int k = 0; k < W * 32; ++k) {
-                if (!((words[k / 32] >> (k % 32)) & 1u)) continue;
-                const int s = k / 64, o = k % 64;
-                const int lane = (o / 32) * 32 + rr, j = o % 32;
-                dst[((static_cast<size_t>(T) * KS + s) * 64 + lane) * 16 + j / 2] |=
-                    static_cast<uint8_t>(0x2 << (4 * (j % 2)));
+    }
+    // Sparse operands: the set bits of every row as column numbers, in slices
+    // of 64 rows (see rsr_refs).
+    auto slices = [&](int64_t R, const std::vector<int>& weight, std::vector<uint32_t>& off) {
+        off.assign(1, 0u);
+        for (int64_t r = 0; r < R; r += 64)  // the last row of a slice is its longest
+            off.push_back(off.back() + static_cast<uint32_t>((weight[std::min(R, r + 64) - 1] + 3) / 4));
+    };
+    std::vector<uint32_t> lo_off, up_off;
+    slices(R_L, lo_weight, lo_off);
+    slices(R_U, up_weight, up_off);
+    const bool sparse =
+        (R_L == 0 || lo_weight[0] > 0) && (R_U == 0 || up_weight[0] > 0) &&
+        256.0 * (static_cast<double>(lo_off.back()) + up_off.back()) <=
+            rsr::kSparseDensity * n * (K - 1) * 64.0 *
+                static_cast<double>(lo_off.size() + up_off.size() - 2);
+    std::vector<uint16_t> lo_idx, up_idx;
+    auto columns = [&](const std::vector<uint32_t>& rows, int64_t R, const std::vector<uint32_t>& off,
+                       std::vector<uint16_t>& idx) {
+        std::vector<uint16_t> cols(static_cast<size_t>(W) * 32);
+        idx.resize(static_cast<size_t>(off.back()) * 256);
+        for (size_t sl = 0; sl + 1 < off.size(); ++sl) {
+            const size_t places = static_cast<size_t>(off[sl + 1] - off[sl]) * 4;
+            for (int64_t k = 0; k < 64; ++k) {
+                const int64_t r = static_cast<int64_t>(sl) * 64 + k;
+                uint16_t* dst = idx.data() + static_cast<size_t>(off[sl]) * 256 + k * 4;
+                size_t c = 0;
+                if (r < R) {
+                    for_bits(rows.data() + r * WR, [&](int b) {
+                        const int w = b / 32;
+                        cols[c++] = static_cast<uint16_t>((w / PW) * n + b - 32 * (w - w % PW));
+                    });
+                    for (; c < places; ++c) cols[c] = cols[c - 1];
+                }  // past the last row: its columns again
+                for (size_t q = 0; q < places; ++q) dst[(q / 4) * 256 + q % 4] = cols[q];
             }
-        };
-        const int64_t TL32 = (R_L + 31) / 32, TU32 = (R_U + 31) / 32;
-        lof32.assign(static_cast<size_t>(TL32) * KS * 1024, 0);
-        upf32.assign(static_cast<size_t>(TU32) * KS * 1024, 0);
-        for (int64_t r = 0; r < R_L; ++r) frag32(lo.data() + r * WR, r, lof32);
-        for (int64_t r = 0; r < R_U; ++r) frag32(up.data() + r * WR, r, upf32);
+        }
+    };
+    if (sparse) {
+        columns(lo, R_L, lo_off, lo_idx);
+        columns(up, R_U, up_off, up_idx);
     }
 
-    rsr_refs* refs = new (std::nothrow) rsr_refs();
-    if (!refs) return fail(ctx, RSR_ENOMEM, "host allocation");
+    std::unique_ptr<rsr_refs, rsr_status (*)(rsr_refs*)> refs(new rsr_refs(), rsr_refs_destroy);
     refs->ctx = ctx;
     refs->n = n;
     refs->K = K;
@@ -584,41 +627,70 @@ rsr_status refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower,
     refs->WR = WR;
     refs->R_L = R_L;
     refs->R_U = R_U;
-    hipError_t e = hipSuccess;
-    auto upload = [&](void** dst, const void* src, size_t bytes) {
-        if (e != hipSuccess || bytes == 0) return;
-        e = rsr::dev_malloc(dst, bytes);
-        if (e == hipSuccess) e = hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice);
+    // One allocation and one copy for all arrays, 256-byte aligned.
+    struct Part {
+        void** dst;
+        const void* src;
+        size_t bytes, at;
     };
-    upload(reinterpret_cast<void**>(&refs->d_lower_nbits), lo.data(), sizeof(uint32_t) * lo.size());
-    upload(reinterpret_cast<void**>(&refs->d_upper_bits), up.data(), sizeof(uint32_t) * up.size());
+    std::vector<Part> parts;
+    size_t total = 0;
+    auto part = [&](auto** dst, const auto& v) {
+        const size_t bytes = sizeof(v[0]) * v.size();
+        if (bytes == 0) return;
+        parts.push_back({reinterpret_cast<void**>(dst), v.data(), bytes, total});
+        total += (bytes + 255) / 256 * 256;
+    };
+    part(&refs->d_lower_nbits, lo);
+    part(&refs->d_upper_bits, up);
+    if (sparse) {
+        refs->sparse = true;
+        part(&refs->d_lower_off, lo_off);
+        part(&refs->d_lower_idx, lo_idx);
+        part(&refs->d_upper_off, up_off);
+        part(&refs->d_upper_idx, up_idx);
+    }
     if (with_mfma) {
         refs->KS = KS;
         refs->TL = TL;
         refs->TU = TU;
-        upload(reinterpret_cast<void**>(&refs->d_lower_frag), lof.data(), lof.size());
-        upload(reinterpret_cast<void**>(&refs->d_lower_cinit), loc.data(), sizeof(int32_t) * loc.size());
-        upload(reinterpret_cast<void**>(&refs->d_upper_frag), upf.data(), upf.size());
-        upload(reinterpret_cast<void**>(&refs->d_upper_cinit), upc.data(), sizeof(int32_t) * upc.size());
-        upload(reinterpret_cast<void**>(&refs->d_lower_frag32), lof32.data(), lof32.size());
-        upload(reinterpret_cast<void**>(&refs->d_upper_frag32), upf32.data(), upf32.size());
         refs->KS4 = KS4;
-        upload(reinterpret_cast<void**>(&refs->d_lower_frag4), lof4.data(), lof4.size());
-        upload(reinterpret_cast<void**>(&refs->d_lower_cinit4), loc4.data(), sizeof(float) * loc4.size());
-        upload(reinterpret_cast<void**>(&refs->d_upper_frag4), upf4.data(), upf4.size());
-        upload(reinterpret_cast<void**>(&refs->d_upper_cinit4), upc4.data(), sizeof(float) * upc4.size());
+        part(&refs->d_lower_frag, lof);
+        part(&refs->d_lower_cinit, loc);
+        part(&refs->d_upper_frag, upf);
+        part(&refs->d_upper_cinit, upc);
+        part(&refs->d_lower_frag32, lof32);
+        part(&refs->d_upper_frag32, upf32);
+        part(&refs->d_lower_frag4, lof4);
+        part(&refs->d_lower_cinit4, loc4);
+        part(&refs->d_upper_frag4, upf4);
+        part(&refs->d_upper_cinit4, upc4);
     }
-    if (e != hipSuccess) {
-        rsr_refs_destroy(refs);
-        return hip_fail(ctx, e, "rsr_refs_create upload");
+    if (total > 0) {
+        std::vector<char> image(total);
+        hipError_t e = rsr::dev_malloc(&refs->d_mem, total);
+        if (e == hipSuccess) {
+            for (const Part& q : parts) {
+                std::memcpy(image.data() + q.at, q.src, q.bytes);
+                *q.dst = static_cast<char*>(refs->d_mem) + q.at;
+            }
+            e = hipMemcpy(refs->d_mem, image.data(), total, hipMemcpyHostToDevice);
+        }
+        if (e != hipSuccess) return hip_fail(ctx, e, "rsr_refs_create upload");
     }
-    rsr_status st = check_consistency(ctx, refs, up);
-    if (st != RSR_OK) {
-        rsr_refs_destroy(refs);
-        return st;
-    }
-    *out = refs;
+    rsr_status st = check_consistency(ctx, refs.get(), up);
+    if (st != RSR_OK) return st;
+    *out = refs.release();
     return RSR_OK;
+}
+
+rsr_status refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
+                       const uint8_t* upper, int64_t R_U, bool matrix_operands, rsr_refs** out) {
+    try {
+        return build_refs(ctx, n, K, lower, R_L, upper, R_U, matrix_operands, out);
+    } catch (const std::bad_alloc&) {
+        return fail(ctx, RSR_ENOMEM, "host allocation");
+    }
 }
 
 }  // namespace rsr
@@ -639,18 +711,7 @@ rsr_status rsr_refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lo
 rsr_status rsr_refs_destroy(rsr_refs* refs) {
     if (!refs) return RSR_EINVAL;
     DeviceGuard g(refs->ctx->device);
-    if (refs->d_lower_nbits) (void)hipFree(refs->d_lower_nbits);
-    if (refs->d_upper_bits) (void)hipFree(refs->d_upper_bits);
-    if (refs->d_lower_frag) (void)hipFree(refs->d_lower_frag);
-    if (refs->d_lower_cinit) (void)hipFree(refs->d_lower_cinit);
-    if (refs->d_upper_frag) (void)hipFree(refs->d_upper_frag);
-    if (refs->d_upper_cinit) (void)hipFree(refs->d_upper_cinit);
-    if (refs->d_lower_frag4) (void)hipFree(refs->d_lower_frag4);
-    if (refs->d_lower_cinit4) (void)hipFree(refs->d_lower_cinit4);
-    if (refs->d_upper_frag4) (void)hipFree(refs->d_upper_frag4);
-    if (refs->d_upper_cinit4) (void)hipFree(refs->d_upper_cinit4);
-    if (refs->d_lower_frag32) (void)hipFree(refs->d_lower_frag32);
-    if (refs->d_upper_frag32) (void)hipFree(refs->d_upper_frag32);
+    if (refs->d_mem) (void)hipFree(refs->d_mem);
     delete refs;
     return RSR_OK;
 }
@@ -777,8 +838,8 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
         return fail(ctx, RSR_EUNSUPPORTED,
                     "the persistent cascade takes LABEL mode on consistent rows, N <= 2^31-1");
     uint32_t* match = mode == RSR_COUNT ? d_match : nullptr;
-    // RSR_AUTO: the cascade for LABEL on consistent rows (each sample stops at
-    // its first match); otherwise the FP4 matrix-core form, which makes the
+    // RSR_AUTO: for LABEL on consistent rows (each sample stops at its first
+    // match) the sparse form, or the cascade for dense rows; otherwise the FP4 matrix-core form, which makes the
     // most tests per second in both modes; popcount beyond 1280 bits.
     if (form == RSR_AUTO && refs->KS4 > 0 && (mode == RSR_COUNT || !refs->consistent))
         form = RSR_MFMA_FP4;
@@ -800,8 +861,13 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
         cb.match[0] = reinterpret_cast<uint32_t*>(ctx->ws.casc_index + 2 * stride);
         cb.match[1] = reinterpret_cast<uint32_t*>(ctx->ws.casc_index + 3 * stride);
         cb.stride = stride;
-        cb.counters = ctx->ws.casc_counters;
-        cb.regions = reinterpret_cast<uint32_t*>(ctx->ws.casc_counters + 16);
+        cb.set_counters(ctx->ws.casc_counters);
+        if (form == RSR_AUTO && refs->sparse) {
+            RSR_HIP(ctx, rsr::launch_dom_sparse(ctx->stream, refs,
+                                                rsr::single_src(d_samples, N, d_flags, nullptr), N,
+                                                cb, ctx->cu_count));
+            return RSR_OK;
+        }
         // The automatic form runs the rounds after round 0 in the FP4
         // matrix-core form when the handle has its operands, with faster
         // growing rounds from kWideRows rows per side on; the popcount form

@@ -128,6 +128,7 @@ struct rsr_refs {
     int n = 0, K = 0, W = 0, WR = 0;  // WR = packed row stride in words
     int64_t R_L = 0, R_U = 0;
     bool consistent = false;            // no upper row lies below a lower row
+    void* d_mem = nullptr;              // one allocation of the arrays below
     uint32_t* d_lower_nbits = nullptr;  // [R_L][WR]: NOT t(r), pad bits 0
     uint32_t* d_upper_bits = nullptr;   // [R_U][WR]: t(r)
     // Matrix-core operands (k_dom_mfma.hip); absent when KS > kMaxMfmaSteps.
@@ -148,6 +149,17 @@ struct rsr_refs {
     // t(r) for lower rows, t(r) for upper rows); ceil(R / 32) tiles per side.
     int8_t* d_lower_frag32 = nullptr;     // [ceil(R_L/32)][KS][64][16]
     int8_t* d_upper_frag32 = nullptr;     // [ceil(R_U/32)][KS][64][16]
+    // Sparse form (k_sparse.hip): a row's set bits as column numbers (plane *
+    // n + component).  64 rows form a slice of chunks of four columns,
+    // [chunk][64 rows][4], as many as its longest row takes; a shorter row
+    // repeats its last column, the last slice its last row.  off[s] is the
+    // first chunk of slice s.  Absent (sparse false) when a row has no bit or
+    // the rows are too dense (kSparseDensity).
+    bool sparse = false;
+    uint32_t* d_lower_off = nullptr;      // [ceil(R_L/64) + 1]
+    uint16_t* d_lower_idx = nullptr;      // columns of NOT t(r)
+    uint32_t* d_upper_off = nullptr;      // [ceil(R_U/64) + 1]
+    uint16_t* d_upper_idx = nullptr;      // columns of t(r)
 };
 
 struct rsr_system {
@@ -235,6 +247,18 @@ __device__ __forceinline__ uint8_t* seg_Y(const SegSrc& s, int j) {
 }
 #endif
 
+// Share of the packed bits that the rows may have set (with the padding of
+// their chunks) for the sparse form to be the automatic LABEL form.  The
+// form's time follows the set bits, the cascade's does not: at 8000 rows per
+// side sparse against cascade, 295 bits and 1e6 samples 210 / 374 us at 0.3,
+// 466 / 633 at 0.5 and 1811 / 1849 at 0.8; 1250 bits and 2e5 samples 248 / 311,
+// 512 / 603 and 1712 / 1498.
+constexpr double kSparseDensity = 0.6;
+
+// Most blocks of a launch of the sparse form (k_sparse.hip), each with an
+// output region of its own.
+constexpr int kSparseRegions = 512;
+
 // Ping-pong buffers of the LABEL-mode cascade (k_dom_cascade): compacted
 // sample words [W][N] and original indices [N], plus one counter per round.
 struct CascadeBuffers {
@@ -242,14 +266,24 @@ struct CascadeBuffers {
     // Most output regions of the matrix-core round 0 (one per block).
     static constexpr int kMaxRegions = 2048;
     // u64 words of the counters allocation: 16 round counters, then
-    // kMaxRegions u32 region counts.
-    static constexpr int kCounterU64 = 16 + kMaxRegions / 2;
+    // kMaxRegions u32 region counts, then the sparse form's region extents.
+    static constexpr int kCounterU64 = 16 + kMaxRegions / 2 + 2 * kSparseRegions;
     uint32_t* words[2] = {nullptr, nullptr};  // [W][stride] each
     int32_t* index[2] = {nullptr, nullptr};   // [stride] each
     uint32_t* match[2] = {nullptr, nullptr};  // [stride] each: match bits of split rounds
     int64_t stride = 0;                       // capacity in samples (>= total)
     uint64_t* counters = nullptr;  // [kMaxRounds], zeroed before the first round
     uint32_t* regions = nullptr;   // [kMaxRegions] (k_casc_head)
+    // (start, count) of the blocks' regions in the two sample lists of the
+    // sparse form, as pairs of i32 in one u64.
+    uint64_t* sparse_regions[2] = {nullptr, nullptr};
+    // Takes the arrays above from one allocation of kCounterU64 words.
+    void set_counters(uint64_t* mem) {
+        counters = mem;
+        regions = reinterpret_cast<uint32_t*>(mem + 16);
+        sparse_regions[0] = mem + 16 + kMaxRegions / 2;
+        sparse_regions[1] = sparse_regions[0] + kSparseRegions;
+    }
 };
 
 // Round boundaries of the cascade: rows [0, first), [first, first*growth), ...
@@ -319,6 +353,10 @@ hipError_t launch_dom_bits(hipStream_t st, const rsr_refs* refs, const uint32_t*
                            int64_t N, int mode, uint8_t* d_flags, uint32_t* d_match);
 hipError_t launch_dom_cascade(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
                               const CascadeBuffers& cb, const CascadeShape& shape, int grid_cap);
+// LABEL mode on a consistent reference set with sparse operands; max_N = the
+// samples of the largest job.
+hipError_t launch_dom_sparse(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
+                             int64_t max_N, const CascadeBuffers& cb, int cus);
 // `cus` (the device's CU count) picks the sample tiles per wave for the grid.
 hipError_t launch_dom_mfma(hipStream_t st, const rsr_refs* refs, const uint32_t* d_samples,
                            int64_t N, int mode, bool fp4, int cus, uint8_t* d_flags,

@@ -33,7 +33,10 @@ namespace {
 
 // kPersist: the persistent LABEL cascade (one round-0 launch and one
 // cooperative launch for every later round, over all jobs of the segment).
-enum Choice { kCascade = 0, kBitsPerJob = 1, kMfmaPerJob = 2, kMfma4PerJob = 3, kPersist = 4 };
+// kSparse: the sparse LABEL form (k_sparse.hip).
+enum Choice {
+    kCascade = 0, kBitsPerJob = 1, kMfmaPerJob = 2, kMfma4PerJob = 3, kPersist = 4, kSparse = 5
+};
 
 struct Segment {
     const rsr_refs* refs = nullptr;
@@ -151,7 +154,7 @@ class CacheReader {
             if (eat('}')) break;
             return false;
         }
-        return (seen & 63) == 63 && e.choice >= kCascade && e.choice <= kPersist &&
+        return (seen & 63) == 63 && e.choice >= kCascade && e.choice <= kSparse &&
                e.chunks >= 0 && e.chunks <= 1024 &&
                (e.choice != kCascade || (e.first >= 1 && e.growth >= 2 && e.split >= 1));
     }
@@ -228,8 +231,7 @@ rsr::CascadeBuffers casc_buffers(const rsr_plan* p) {
     cb.match[0] = reinterpret_cast<uint32_t*>(p->d_casc_index + 2 * p->casc_cap);
     cb.match[1] = reinterpret_cast<uint32_t*>(p->d_casc_index + 3 * p->casc_cap);
     cb.stride = p->casc_cap;
-    cb.counters = p->d_casc_counters;
-    cb.regions = reinterpret_cast<uint32_t*>(p->d_casc_counters + 16);
+    cb.set_counters(p->d_casc_counters);
     return cb;
 }
 
@@ -258,6 +260,8 @@ hipError_t enqueue_classify(const rsr_plan* p, int si, hipStream_t st, Choice ch
                                         reinterpret_cast<unsigned long long*>(p->d_casc_counters + 15),
                                         p->ctx->cu_count);
     }
+    if (choice == kSparse)
+        return rsr::launch_dom_sparse(st, s.refs, src, s.max_N, casc_buffers(p), p->ctx->cu_count);
     if (choice == kCascade) {
         const rsr::CascadeBuffers cb = casc_buffers(p);
         hipError_t e = rsr::launch_fill_u64(st, cb.counters, rsr::CascadeBuffers::kMaxRounds, 0);
@@ -319,6 +323,7 @@ bool choice_runs(const Segment& s) {
         case kBitsPerJob: return true;
         case kMfmaPerJob: return s.refs->KS > 0;
         case kMfma4PerJob: return s.refs->KS4 > 0;
+        case kSparse: return s.refs->consistent && s.refs->sparse;
         case kPersist: return s.refs->consistent && rsr::casc_persist_supported(s.refs);
     }
     return false;
@@ -406,9 +411,10 @@ rsr_status tune_segment(rsr_plan* p, int si) {
         if (s.refs->KS4 > 0 && rsr::casc_head_supported(s.refs))
             forms.push_back({kCascade, rsr::mfma_head_shape()});
         if (rsr::casc_persist_supported(s.refs)) forms.push_back({kPersist, rsr::mfma_head_shape()});
+        if (s.refs->sparse) forms.push_back({kSparse, rsr::CascadeShape{}});
         st = trial(forms);
-        // The persistent cascade keeps its own round sizes.
-        if (st != RSR_OK || s.choice == kPersist) {
+        // The persistent cascade and the sparse form keep their own round sizes.
+        if (st != RSR_OK || s.choice == kPersist || s.choice == kSparse) {
             s.tuned_ms = best / 2.0f * scale;
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
@@ -521,10 +527,10 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
             s.n = jb.refs->n;
             s.K = jb.refs->K;
             s.W = jb.refs->W;
-            s.choice = jb.refs->consistent ? kCascade : kBitsPerJob;
-            // Untuned, a cascade takes the shape of rsr_classify's automatic
-            // form: matrix-core rounds when the reference handle has FP4
-            // operands, growing faster from kWideRows rows per side on.
+            s.choice = !jb.refs->consistent ? kBitsPerJob : jb.refs->sparse ? kSparse : kCascade;
+            // Untuned, a segment takes rsr_classify's automatic form, and a
+            // cascade its shape: matrix-core rounds when the reference handle
+            // has FP4 operands, growing faster from kWideRows rows per side on.
             const int64_t rows = std::max(jb.refs->R_L, jb.refs->R_U);
             if (jb.refs->KS4 > 0)
                 s.shape = rows >= rsr::kWideRows ? rsr::mfma_wide_shape() : rsr::mfma_tail_shape();

@@ -1,0 +1,138 @@
+"""The sparse LABEL form (the automatic one on consistent rows that constrain
+few components) where it can go wrong: tile, slice and round boundaries, ragged
+widths, more tiles than blocks, empty sides, unaligned flags and jobs of a
+plan whose sizes differ.  Small cases against the oracle, large ones against
+the popcount form."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2604_17066_amd as R
+from helpers import unpack_states
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(rng, R_L, R_U, n, K, bits):
+    """Consistent rows: component 0 is 0 in every lower and K-1 in every upper
+    row; about `bits` further components are constrained, in rows of mixed
+    sizes."""
+    lower = np.full((R_L, n), K - 1, dtype=np.uint8)
+    upper = np.zeros((R_U, n), dtype=np.uint8)
+    for rows, at, far in ((lower, 0, K - 1), (upper, K - 1, 0)):
+        share = rng.uniform(0.3, 2.0, rows.shape[0])[:, None] * bits / n
+        hit = rng.random(rows.shape) < share
+        level = rng.integers(0, K, rows.shape).astype(np.uint8)
+        rows[hit] = level[hit]
+        rows[:, 0] = at
+    return lower, upper
+
+
+def _model(n, K, bits):
+    q = max(0.5, 1.0 - 3.0 / bits)
+    p = np.full((n, K), (1.0 - q) / (K - 1))
+    p[:, K - 1] = 1.0 - (1.0 - q) / (K - 1) * (K - 1)
+    p[0] = 1.0 / K
+    return p
+
+
+def _flags(ctx, model, refs, seed, N, form=R.RSR_AUTO, offset=0):
+    xs = R.rsr_sample(ctx, model, seed, 0, 0, N)
+    out = torch.full((N + offset + 8,), 77, dtype=torch.uint8, device=ctx.device)
+    R.rsr_classify(ctx, refs, xs, N, form=form, flags=out[offset:offset + N])
+    got = out.cpu().numpy()
+    assert (got[:offset] == 77).all() and (got[offset + N:] == 77).all()
+    return xs, got[offset:offset + N]
+
+
+@pytest.mark.parametrize("n,K,R_L,R_U,N,offset", [
+    (5, 2, 1, 1, 1, 0),
+    (31, 2, 63, 64, 127, 0),
+    (32, 2, 64, 65, 128, 0),
+    (33, 2, 65, 300, 129, 3),
+    (70, 3, 255, 257, 4097, 1),
+    (40, 4, 384, 385, 2047, 2),
+    (64, 2, 700, 9, 10_001, 0),
+    (295, 2, 0, 500, 3000, 0),
+    (295, 2, 500, 0, 3001, 0),
+    (295, 2, 1500, 4500, 6000, 5),
+    (1250, 2, 400, 450, 2500, 0),
+    (21, 16, 300, 330, 3000, 0),
+])
+def test_small_against_the_oracle(rsr_ctx, n, K, R_L, R_U, N, offset):
+    rng = np.random.default_rng(n * 31 + N)
+    bits = min(12, max(1, n // 3))
+    lower, upper = _rows(rng, R_L, R_U, n, K, bits)
+    model = R.Model(rsr_ctx, _model(n, K, bits))
+    refs = R.Refs(rsr_ctx, n, K, lower, upper)
+    assert refs.consistent
+    xs, got = _flags(rsr_ctx, model, refs, 11, N, offset=offset)
+    want, _, _ = oracle.classify(lower, upper, unpack_states(xs.cpu().numpy(), n, K), mode=0)
+    np.testing.assert_array_equal(got, want)
+    if N > 2000 and R_L and R_U:
+        assert {1, 2} <= set(np.unique(got).tolist())
+
+
+# More tiles than blocks (512 of them): tiles of 2048 samples up to about 300
+# bits, of 512 at 1250, of 128 at 4096; three rounds from 6145 rows on.
+@pytest.mark.parametrize("n,K,R_L,R_U,N", [
+    (60, 2, 900, 7000, 1_100_001),
+    (295, 2, 7000, 400, 1_050_000),
+    (1250, 2, 900, 900, 270_003),
+    (4096, 2, 300, 500, 66_001),
+    (295, 3, 20, 20, 600_001),
+])
+def test_large_against_the_popcount_form(rsr_ctx, n, K, R_L, R_U, N):
+    rng = np.random.default_rng(n + N)
+    lower, upper = _rows(rng, R_L, R_U, n, K, 14)
+    model = R.Model(rsr_ctx, _model(n, K, 14))
+    refs = R.Refs(rsr_ctx, n, K, lower, upper)
+    assert refs.consistent
+    _, got = _flags(rsr_ctx, model, refs, 12, N)
+    _, want = _flags(rsr_ctx, model, refs, 12, N, form=R.RSR_POPCOUNT)
+    np.testing.assert_array_equal(got, want)
+    assert {1, 2} <= set(np.unique(got).tolist())
+
+
+def test_rows_without_a_bit_and_dense_rows_keep_their_labels(rsr_ctx):
+    rng = np.random.default_rng(3)
+    n, N = 40, 5000
+    model = R.Model(rsr_ctx, np.full((n, 2), 0.5))
+    dense = rng.random((300, n)) < 0.9
+    for lower, upper in ((np.ones((2, n), np.uint8), np.zeros((0, n), np.uint8)),
+                         (np.zeros((0, n), np.uint8), np.zeros((3, n), np.uint8)),
+                         (np.zeros((0, n), np.uint8), dense.astype(np.uint8))):
+        refs = R.Refs(rsr_ctx, n, 2, lower, upper)
+        xs, got = _flags(rsr_ctx, model, refs, 4, N)
+        want, _, _ = oracle.classify(lower, upper, unpack_states(xs.cpu().numpy(), n, 2), mode=0)
+        np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("sizes", [(1, 127, 128, 129), (5000, 3, 2048, 70_001, 64),
+                                   tuple([4099] * 40)])
+def test_jobs_of_a_plan(rsr_ctx, sizes):
+    """Jobs that end inside a tile, in one round and in the listed rounds."""
+    n, K = 60, 3
+    rng = np.random.default_rng(len(sizes))
+    g = {"n_nodes": n + 1, "edge_u": np.arange(n), "edge_v": np.arange(1, n + 1), "source": 0,
+         "sink": n}
+    for rows in (50, 6500):
+        lower, upper = _rows(rng, rows, rows, n, K, 12)
+        refs = R.Refs(rsr_ctx, n, K, lower, upper)
+        assert refs.consistent
+        system = R.System(rsr_ctx, g, K=K, level=1)
+        model = R.Model(rsr_ctx, _model(n, K, 12))
+        jobs = [{"model": model, "refs": refs, "system": system, "seed": 50 + k, "N": N,
+                 "buffers": R.Buffers(rsr_ctx, n, K, N)} for k, N in enumerate(sizes)]
+        plan = R.Plan(rsr_ctx, jobs, tune=False)
+        for _ in range(2):
+            for job in jobs:
+                job["buffers"].flags.fill_(9)
+            plan.run()
+            plan.results()
+            for job in jobs:
+                b = job["buffers"]
+                want = R.rsr_classify(rsr_ctx, refs, b.samples, job["N"], form=R.RSR_POPCOUNT)
+                np.testing.assert_array_equal(b.flags.cpu().numpy(), want.cpu().numpy())
+        plan.close()
