@@ -293,11 +293,10 @@ rsr_status rsr_importance(rsr_ctx* ctx, const rsr_model* model, const uint32_t* 
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * rsr_eval_unknown without any allocation.  Same arguments, outputs and
  * errors as rsr_eval_unknown, except that the list of unclassified samples
- * and its counter live in a fixed scratch array of the library, one per
- * device, of 16 MiB + 64 bytes, held until the process ends; so N is limited
+ * lives in a fixed scratch array of the library, one per
+ * device, of 16 MiB + 4 KiB, held until the process ends; so N is limited
  * to 2^22 samples (EINVAL beyond), and host-callback systems, which stage
- * samples in allocated host and device memory, are EUNSUPPORTED.  The
- * counter is cleared by a kernel at the start of every call.  Every call on
+ * samples in allocated host and device memory, are EUNSUPPORTED.  Every call on
  * one device shares that device's scratch: calls that overlap on one device
  * (on different streams or from different host threads) race, so the
  * caller must order them. */

@@ -18,6 +18,7 @@
 // search; otherwise the flow is recomputed from zero at the new capacities,
 // and restored from a copy if the step is undone.
 #include "graph_search.h"
+#include "sample_list.h"
 
 namespace rsr {
 namespace {
@@ -142,12 +143,11 @@ __device__ void load_caps(const FlowSets& f, const uint32_t* xs, int64_t stride,
 
 __global__ __launch_bounds__(kFlowBlock) void k_flow_eval(
     SegSrc seg, int PW, int K, const uint32_t* __restrict__ edges, int n_edges, int n_nodes,
-    int source, int sink, int demand, const int32_t* __restrict__ list,
-    const unsigned long long* __restrict__ count_ptr, int which,
+    int source, int sink, int demand, SampleList list, int which,
     unsigned long long* __restrict__ n_evaluated) {
     extern __shared__ uint32_t lds[];
-    const int64_t N = seg.total;
-    const int64_t total = which == RSR_ALL ? N : static_cast<int64_t>(*count_ptr);
+    __shared__ uint32_t before[kListRegions + 1];
+    const int64_t total = which == RSR_ALL ? seg.total : list_prefix(list, before);
     if (blockIdx.x == 0 && threadIdx.x == 0 && n_evaluated)
         *n_evaluated = static_cast<unsigned long long>(total);
     const int wave = threadIdx.x >> 6;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kFlowBlock) void k_flow_eval(
     const FlowSets f = flow_sets(lds + n_edges + wave * flow_words(n_nodes, n_edges), n_nodes, n_edges);
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kFlowWaves;
     for (int64_t j = first + wave; j < total; j += stride) {
-        const int64_t g = which == RSR_ALL ? j : static_cast<int64_t>(list[j]);
+        const int64_t g = which == RSR_ALL ? j : list_at(list, before, static_cast<uint32_t>(j));
         int job;
         int64_t h, xstride;
         seg_locate(seg, g, job, h);
@@ -247,15 +247,14 @@ size_t flow_lds_bytes(const rsr_system* sys) {
 }
 
 hipError_t launch_flow_eval(hipStream_t st, const rsr_system* sys, const SegSrc& seg,
-                            const int32_t* d_list, const uint64_t* d_count, int which,
-                            uint64_t* d_n_evaluated, int grid_blocks) {
+                            const SampleList& list, int which, uint64_t* d_n_evaluated,
+                            int grid_blocks) {
     const int64_t need = (seg.total + kFlowWaves - 1) / kFlowWaves;
     int blocks = static_cast<int>(need < grid_blocks ? need : grid_blocks);
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(k_flow_eval, dim3(blocks), dim3(kFlowBlock), flow_lds_bytes(sys), st, seg,
                        plane_words(sys->n_edges), sys->K, sys->d_edges, sys->n_edges, sys->n_nodes,
-                       sys->source, sys->sink, sys->level, d_list,
-                       reinterpret_cast<const unsigned long long*>(d_count), which,
+                       sys->source, sys->sink, sys->level, list, which,
                        reinterpret_cast<unsigned long long*>(d_n_evaluated));
     return hipGetLastError();
 }

@@ -39,12 +39,12 @@
 // rounds: 119-node / 295-edge network, 1e4 rows per side, 1e6 samples 150 -> 62
 // us; 500 / 1250, 4e4 rows, 262144 samples 343 -> 60 us; three-state edges,
 // 2.5e4 rows, 1e6 samples 343 -> 91 us.
-#include <type_traits>
-
-#include "rsr_internal.h"
+#include "bits.h"
 
 namespace rsr {
 namespace {
+
+using namespace bits;
 
 constexpr int kThreads = 512;
 constexpr int kMinWaves = 4;  // per SIMD: two blocks in a CU
@@ -93,44 +93,6 @@ static_assert(sizeof(TileMasks) % 16 == 0, "the tile behind it is read 16 bytes 
 
 __device__ __forceinline__ uint32_t nibble_bytes(uint32_t v) {
     return (v * 0x00204081u) & 0x01010101u;  // bit c -> byte c
-}
-
-// One step of the transpose: swaps the upper J-bit halves of the words k with
-// the lower ones of the words k + J (k without bit J).
-template <int J>
-__device__ __forceinline__ void transpose_step(uint32_t (&a)[32]) {
-    constexpr uint32_t m = J == 4 ? 0x0F0F0F0Fu : J == 2 ? 0x33333333u : 0x55555555u;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int k = (i & (J - 1)) | ((i & ~(J - 1)) << 1);
-        const uint32_t x = a[k], y = a[k + J];
-        if (J == 16) {
-            a[k] = __builtin_amdgcn_perm(y, x, 0x05040100u);
-            a[k + J] = __builtin_amdgcn_perm(y, x, 0x07060302u);
-        } else if (J == 8) {
-            a[k] = __builtin_amdgcn_perm(y, x, 0x06020400u);
-            a[k + J] = __builtin_amdgcn_perm(y, x, 0x07030501u);
-        } else {
-            a[k] = (x & m) | ((y << J) & ~m);
-            a[k + J] = ((x >> J) & m) | (y & ~m);
-        }
-    }
-}
-
-// In place: bit i of a[k] becomes bit k of a[i].
-__device__ __forceinline__ void transpose32(uint32_t (&a)[32]) {
-    transpose_step<16>(a);
-    transpose_step<8>(a);
-    transpose_step<4>(a);
-    transpose_step<2>(a);
-    transpose_step<1>(a);
-}
-
-// The pointers of a job table are loaded from memory, so the compiler has to be
-// told that they point to global memory.
-template <class T>
-__device__ __forceinline__ T* global_ptr(T* p) {
-    return (T*)(__attribute__((address_space(1))) T*)p;
 }
 
 // Four 32-bit words at a 4-byte aligned address.
@@ -245,24 +207,6 @@ __device__ __forceinline__ void put_columns(uint32_t (&a)[32], const SparseShape
         for (int k = 0; k < 31; ++k)
             if (k < bits) at[k << (lg + 2)] = a[k];
     }
-}
-
-// OR of v over the lanes that hold the same samples as this one (equal lane
-// numbers modulo 1 << lg): rotations within the rows of 16 lanes, then swaps
-// of the rows and of the wave's halves.
-__device__ __forceinline__ uint32_t or_rows(uint32_t v, int lg) {
-    auto ror = [](uint32_t x, auto ctrl) {
-        return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
-            0, static_cast<int>(x), decltype(ctrl)::value, 0xF, 0xF, true));
-    };
-    if (lg < 1) v |= ror(v, std::integral_constant<int, 0x121>{});
-    if (lg < 2) v |= ror(v, std::integral_constant<int, 0x122>{});
-    if (lg < 3) v |= ror(v, std::integral_constant<int, 0x124>{});
-    if (lg < 4) v |= ror(v, std::integral_constant<int, 0x128>{});
-    const auto h = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = h[0] | h[1];
-    const auto w = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return w[0] | w[1];
 }
 
 // Both sides' rows on the tile; the matches go to the masks.

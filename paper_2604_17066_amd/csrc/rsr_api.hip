@@ -58,7 +58,7 @@ rsr_status ensure_list(rsr_ctx* ctx, int64_t N) {
         ctx->ws.list_cap = 0;
         if (e != hipSuccess) return hip_error(ctx, e, "hipFree(unknown list)");
     }
-    hipError_t e = dev_malloc(&ctx->ws.list, sizeof(int32_t) * static_cast<size_t>(N));
+    hipError_t e = dev_malloc(&ctx->ws.list, SampleList::bytes(N));
     if (e != hipSuccess) return hip_error(ctx, e, "unknown-sample list");
     ctx->ws.list_cap = N;
     return RSR_OK;
@@ -786,6 +786,13 @@ rsr_status rsr_system_create(rsr_ctx* ctx, const rsr_system_desc* d, rsr_system*
     s->level = d->level;
     s->source = global ? 0 : d->source;
     s->sink = global ? 0 : d->sink;
+    std::vector<int> degree(d->n_nodes, 0);
+    for (uint32_t uv : packed) {
+        ++degree[uv & 0xFFFFu];
+        ++degree[uv >> 16];
+    }
+    s->tree_from = static_cast<int>(std::min_element(degree.begin(), degree.end()) - degree.begin());
+    s->class_from = static_cast<int>(std::max_element(degree.begin(), degree.end()) - degree.begin());
     hipError_t e = rsr::dev_malloc(&s->d_edges, sizeof(uint32_t) * packed.size());
     if (e == hipSuccess)
         e = hipMemcpy(s->d_edges, packed.data(), sizeof(uint32_t) * packed.size(),
@@ -912,16 +919,15 @@ rsr_status rsr_eval_unknown(rsr_ctx* ctx, const rsr_system* sys, const uint32_t*
     DeviceGuard g(ctx->device);
     if (sys->kind == RSR_SYS_HOST_CALLBACK)
         return rsr::eval_callback(ctx, sys, d_samples, N, d_flags, which, d_Y, d_n_evaluated);
-    uint64_t* counter = ctx->ws.counters + 8;
     const rsr::SegSrc seg = rsr::single_src(d_samples, N, const_cast<uint8_t*>(d_flags), d_Y);
+    rsr::SampleList list;
     if (which == RSR_UNKNOWN_ONLY) {
         rsr_status st = rsr::ensure_list(ctx, N);
         if (st != RSR_OK) return st;
-        RSR_HIP(ctx, rsr::launch_fill_u64(ctx->stream, counter, 1, 0));
-        RSR_HIP(ctx, rsr::launch_label(ctx->stream, seg, ctx->ws.list, counter, ctx->cu_count * 16));
+        list = rsr::SampleList(ctx->ws.list);
+        RSR_HIP(ctx, rsr::launch_label(ctx->stream, seg, list));
     }
-    RSR_HIP(ctx, rsr::launch_bfs(ctx->stream, sys, seg, ctx->ws.list, counter, which,
-                                 d_n_evaluated, ctx->cu_count * 8));
+    RSR_HIP(ctx, rsr::launch_eval(ctx->stream, sys, seg, list, which, d_n_evaluated, ctx->cu_count));
     return RSR_OK;
 }
 

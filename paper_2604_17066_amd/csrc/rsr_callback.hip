@@ -14,42 +14,45 @@
 //   boundary search: the picked samples are gathered the same way, each walk
 //     runs on the host, and the rows are copied back and written for the
 //     valid picks only (k_cb_rows).
-#include <algorithm>
-#include <numeric>
 #include <string>
 #include <vector>
 
-#include "rsr_internal.h"
+#include "sample_list.h"
 
 namespace rsr {
 namespace {
 
 constexpr int kBlock = 256;
 
-// out[j][w] = word w of sample idx(j), for j < count; idx(j) = list[j] (i32),
-// picks[j] (i64), or j when both are null.  Picks outside 0..N-1 are skipped.
+// out[j][w] = word w of sample idx(j), for j < count; idx(j) = entry j of the
+// list, picks[j] (i64), or j when both are absent.  Picks outside 0..N-1 are
+// skipped.
 __global__ __launch_bounds__(kBlock) void k_cb_gather(const uint32_t* __restrict__ xs, int64_t N,
-                                                      int W, const int32_t* __restrict__ list,
+                                                      int W, SampleList list,
                                                       const int64_t* __restrict__ picks,
-                                                      const unsigned long long* __restrict__ d_count,
                                                       int64_t count, uint32_t* __restrict__ out) {
-    const int64_t total = d_count ? static_cast<int64_t>(*d_count) : count;
+    __shared__ uint32_t before[kListRegions + 1];
+    if (list.regions) list_prefix(list, before);
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-    for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < total * W;
+    for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < count * W;
          k += stride) {
         const int64_t j = k / W;
         const int w = static_cast<int>(k - j * W);
-        const int64_t h = list ? static_cast<int64_t>(list[j]) : (picks ? picks[j] : j);
+        const int64_t h = list.regions ? list_at(list, before, static_cast<uint32_t>(j))
+                                       : (picks ? picks[j] : j);
         if (h < 0 || h >= N) continue;
         out[k] = xs[static_cast<int64_t>(w) * N + h];
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_cb_scatter_y(const int32_t* __restrict__ list,
+__global__ __launch_bounds__(kBlock) void k_cb_scatter_y(SampleList list,
                                                          const uint8_t* __restrict__ y, int64_t count,
                                                          uint8_t* __restrict__ Y) {
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (j < count) Y[list[j]] = y[j];
+    __shared__ uint32_t before[kListRegions + 1];
+    list_prefix(list, before);
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+    for (int64_t j = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; j < count; j += stride)
+        Y[list_at(list, before, static_cast<uint32_t>(j))] = y[j];
 }
 
 // rows[j][*] = staged[j][*] for every pick with a valid side (< 2).
@@ -136,54 +139,40 @@ rsr_status eval_callback(rsr_ctx* ctx, const rsr_system* sys, const uint32_t* d_
     const int n = sys->n_edges, K = sys->K, W = sample_words(n, K);
     hipStream_t st = ctx->stream;
     int64_t count = N;
-    const int32_t* list = nullptr;
+    SampleList list;
     if (which == RSR_UNKNOWN_ONLY) {
         rsr_status s = ensure_list(ctx, N);
         if (s != RSR_OK) return s;
-        uint64_t* counter = ctx->ws.counters + 8;
-        CB_HIP(ctx, launch_fill_u64(st, counter, 1, 0));
+        list = SampleList(ctx->ws.list);
         const SegSrc seg = single_src(d_samples, N, const_cast<uint8_t*>(d_flags), d_Y);
-        CB_HIP(ctx, launch_label(st, seg, ctx->ws.list, counter, ctx->cu_count * 16));
-        CB_HIP(ctx, hipMemcpyAsync(ctx->ws.host_counts + 8, counter, sizeof(uint64_t),
+        CB_HIP(ctx, launch_label(st, seg, list));
+        std::vector<int2> regions(kListRegions);
+        CB_HIP(ctx, hipMemcpyAsync(regions.data(), list.regions, sizeof(int2) * kListRegions,
                                    hipMemcpyDeviceToHost, st));
         CB_HIP(ctx, hipStreamSynchronize(st));
-        count = static_cast<int64_t>(ctx->ws.host_counts[8]);
-        list = ctx->ws.list;
+        count = 0;
+        for (const int2& r : regions) count += r.y;
     }
     if (count > 0) {
         rsr_status s = ensure_stage(ctx, count * W, count, 0);
         if (s != RSR_OK) return s;
         CallbackStage& cb = ctx->ws.cb;
         hipLaunchKernelGGL(k_cb_gather, dim3(grid_for(count * W)), dim3(kBlock), 0, st, d_samples,
-                           N, W, list, static_cast<const int64_t*>(nullptr),
-                           static_cast<const unsigned long long*>(nullptr), count, cb.d_words);
+                           N, W, list, static_cast<const int64_t*>(nullptr), count, cb.d_words);
         CB_HIP(ctx, hipGetLastError());
         CB_HIP(ctx, hipMemcpyAsync(cb.h_words, cb.d_words, sizeof(uint32_t) * count * W,
                                    hipMemcpyDeviceToHost, st));
-        std::vector<int32_t> order_idx;
-        if (list) {
-            order_idx.resize(static_cast<size_t>(count));
-            CB_HIP(ctx, hipMemcpyAsync(order_idx.data(), list, sizeof(int32_t) * count,
-                                       hipMemcpyDeviceToHost, st));
-        }
         CB_HIP(ctx, hipStreamSynchronize(st));
-        // The list is filled by atomics, so its order varies; the callback is
-        // called in increasing sample index, which makes the call sequence
-        // reproducible.
-        std::vector<int64_t> order(static_cast<size_t>(count));
-        std::iota(order.begin(), order.end(), int64_t{0});
-        if (list)
-            std::sort(order.begin(), order.end(),
-                      [&](int64_t a, int64_t b) { return order_idx[a] < order_idx[b]; });
+        // The list is in sample order, and so is the sequence of calls.
         std::vector<uint8_t> x(static_cast<size_t>(n));
-        for (int64_t j : order) {
+        for (int64_t j = 0; j < count; ++j) {
             decode(cb.h_words + j * W, n, K, x.data());
             const int y = call_phi(sys, x.data());
             if (y < 0)
                 return set_error(ctx, RSR_EINVAL, "system function returned a negative state");
             cb.h_bytes[j] = static_cast<uint8_t>(y);
         }
-        if (list) {
+        if (list.regions) {
             CB_HIP(ctx, hipMemcpyAsync(cb.d_bytes, cb.h_bytes, static_cast<size_t>(count),
                                        hipMemcpyHostToDevice, st));
             hipLaunchKernelGGL(k_cb_scatter_y, dim3(grid_for(count)), dim3(kBlock), 0, st, list,
@@ -210,8 +199,7 @@ rsr_status boundary_callback(rsr_ctx* ctx, const rsr_system* sys, const uint32_t
     if (s != RSR_OK) return s;
     CallbackStage& cb = ctx->ws.cb;
     hipLaunchKernelGGL(k_cb_gather, dim3(grid_for(n_pick * W)), dim3(kBlock), 0, st, d_samples, N,
-                       W, static_cast<const int32_t*>(nullptr), d_pick,
-                       static_cast<const unsigned long long*>(nullptr), n_pick, cb.d_words);
+                       W, SampleList(), d_pick, n_pick, cb.d_words);
     CB_HIP(ctx, hipGetLastError());
     CB_HIP(ctx, hipMemcpyAsync(cb.h_words, cb.d_words, sizeof(uint32_t) * n_pick * W,
                                hipMemcpyDeviceToHost, st));

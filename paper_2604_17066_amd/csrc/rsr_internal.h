@@ -81,7 +81,7 @@ struct CallbackStage {
 struct Workspace {
     uint64_t* counters = nullptr;      // 16 u64 device counters
     uint64_t* count_part = nullptr;    // [kMaxReduceBlocks][8] u64 partial counts
-    int32_t* list = nullptr;           // unknown-sample index list
+    void* list = nullptr;              // unknown-sample list (SampleList)
     int64_t list_cap = 0;
     uint32_t* grad_part = nullptr;     // [RSR_MAX_BITS * kMaxGradBlocks + kMaxGradBlocks] u32
     uint64_t* host_counts = nullptr;   // pinned, 16 u64
@@ -167,6 +167,10 @@ struct rsr_system {
     int kind = RSR_SYS_ST_CONNECTIVITY;
     int n_nodes = 0, n_edges = 0, K = 0, level = 0, source = 0, sink = 0;
     uint32_t* d_edges = nullptr;  // [n_edges] packed (u | v << 16); graph systems only
+    // Global connectivity: where the spanning-tree search and the class of
+    // two-edge-connected nodes start (k_eval.hip).  All edges of the first may
+    // be tree edges, so it is a node of least degree, the other of the most.
+    int tree_from = 0, class_from = 0;
     // RSR_SYS_HOST_CALLBACK: the system state of a state vector, on the host.
     int32_t (*phi)(const uint8_t* x, int32_t n, void* user) = nullptr;
     void* user = nullptr;
@@ -202,6 +206,21 @@ struct SegSrc {
     const int64_t* offsets;  // [n_jobs + 1]
     int32_t n_jobs;
     int64_t total;
+};
+
+// The list of unclassified samples (sample_list.h) in one allocation of
+// bytes(N): the blocks' regions (start, count) and room for N indices.
+constexpr int kListRegions = 512;
+struct SampleList {
+    int2* regions = nullptr;   // [kListRegions]
+    int32_t* index = nullptr;  // [N]
+    SampleList() = default;
+    explicit SampleList(void* mem)
+        : regions(static_cast<int2*>(mem)),
+          index(reinterpret_cast<int32_t*>(static_cast<int2*>(mem) + kListRegions)) {}
+    static size_t bytes(int64_t N) {
+        return sizeof(int2) * kListRegions + sizeof(int32_t) * static_cast<size_t>(N);
+    }
 };
 
 inline SegSrc single_src(const uint32_t* samples, int64_t N, uint8_t* flags, uint8_t* Y) {
@@ -398,17 +417,17 @@ void set_barrier_timeout(int64_t ticks);
 bool casc_head_supported(const rsr_refs* refs);
 hipError_t launch_casc_head(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
                             const CascadeBuffers& cb, int last);
-hipError_t launch_label(hipStream_t st, const SegSrc& seg, int32_t* d_list, uint64_t* d_counter,
-                        int grid_cap);
-hipError_t launch_bfs(hipStream_t st, const rsr_system* sys, const SegSrc& seg,
-                      const int32_t* d_list, const uint64_t* d_count, int which,
-                      uint64_t* d_n_evaluated, int grid_blocks);
+// Y of the classified samples and the list of the others.
+hipError_t launch_label(hipStream_t st, const SegSrc& seg, const SampleList& list);
+// The system function of the listed samples (RSR_UNKNOWN_ONLY) or of all.
+hipError_t launch_eval(hipStream_t st, const rsr_system* sys, const SegSrc& seg,
+                       const SampleList& list, int which, uint64_t* d_n_evaluated, int cus);
 hipError_t launch_fill_u64(hipStream_t st, uint64_t* p, int64_t count, uint64_t value);
 size_t boundary_lds_bytes(const rsr_system* sys);
 size_t flow_lds_bytes(const rsr_system* sys);
 hipError_t launch_flow_eval(hipStream_t st, const rsr_system* sys, const SegSrc& seg,
-                            const int32_t* d_list, const uint64_t* d_count, int which,
-                            uint64_t* d_n_evaluated, int grid_blocks);
+                            const SampleList& list, int which, uint64_t* d_n_evaluated,
+                            int grid_blocks);
 hipError_t launch_boundary_flow(hipStream_t st, const rsr_system* sys, const uint32_t* xs,
                                 int64_t N, const int64_t* d_pick, int64_t n_pick, uint8_t* d_rows,
                                 uint8_t* d_side, int grid_cap);
@@ -449,7 +468,7 @@ hipError_t launch_importance(hipStream_t st, int n, const double* d_p64, const u
                              const uint8_t* d_Y, int64_t N, uint32_t* d_partial, float* d_I);
 
 // Scratch of rsr_eval_unknown_noalloc (rsr_noalloc.hip): a file-scope device
-// array holding a counter and a list of up to kNoAllocMaxSamples indices.
+// array holding a SampleList of up to kNoAllocMaxSamples indices.
 constexpr int64_t kNoAllocMaxSamples = int64_t{1} << 22;
 constexpr int RSR_MAX_DEVICES = 64;
 // This device's address of the array, looked up once per device.

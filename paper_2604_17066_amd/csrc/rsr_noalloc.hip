@@ -1,5 +1,5 @@
 // rsr_eval_unknown_noalloc: Stage-2 evaluation with its scratch memory (the
-// list of unclassified samples and its counter) in a file-scope device array
+// list of unclassified samples) in a file-scope device array
 // instead of the context's workspace, so the call never allocates.
 //
 // `scratch` exists once per device that loads the library and lives until
@@ -15,10 +15,9 @@
 namespace rsr {
 namespace {
 
-// Counter (8 u64 slots, 64 bytes, of which the first is used) followed by the
-// list of up to kNoAllocMaxSamples sample indices.
-constexpr int64_t kCounterWords = 16;  // u32 words
-constexpr size_t kScratchWords = static_cast<size_t>(kCounterWords) + kNoAllocMaxSamples;
+// A SampleList: the regions' extents (two u32 each) followed by up to
+// kNoAllocMaxSamples sample indices.
+constexpr size_t kScratchWords = 2 * kListRegions + static_cast<size_t>(kNoAllocMaxSamples);
 
 __device__ __align__(256) uint32_t scratch[kScratchWords];
 
@@ -71,21 +70,12 @@ extern "C" rsr_status rsr_eval_unknown_noalloc(rsr_ctx* ctx, const rsr_system* s
     if (hipGetDevice(&prev) != hipSuccess) return rsr::set_error(ctx, RSR_EHIP, "hipGetDevice");
     if (prev != ctx->device && hipSetDevice(ctx->device) != hipSuccess)
         return rsr::set_error(ctx, RSR_EHIP, "hipSetDevice");
-    uint64_t* counter = static_cast<uint64_t*>(ctx->noalloc_scratch);
-    int32_t* list = reinterpret_cast<int32_t*>(static_cast<uint32_t*>(ctx->noalloc_scratch) +
-                                               rsr::kCounterWords);
+    const rsr::SampleList list(ctx->noalloc_scratch);
     const rsr::SegSrc seg = rsr::single_src(d_samples, N, const_cast<uint8_t*>(d_flags), d_Y);
     hipError_t e = hipSuccess;
-    if (which == RSR_UNKNOWN_ONLY) {
-        // The counter keeps the previous call's value: clear it with a kernel
-        // (not a memset node, so the call can also be captured into a graph).
-        e = rsr::launch_fill_u64(ctx->stream, counter, 1, 0);
-        if (e == hipSuccess)
-            e = rsr::launch_label(ctx->stream, seg, list, counter, ctx->cu_count * 16);
-    }
+    if (which == RSR_UNKNOWN_ONLY) e = rsr::launch_label(ctx->stream, seg, list);
     if (e == hipSuccess)
-        e = rsr::launch_bfs(ctx->stream, sys, seg, list, counter, which, d_n_evaluated,
-                            ctx->cu_count * 8);
+        e = rsr::launch_eval(ctx->stream, sys, seg, list, which, d_n_evaluated, ctx->cu_count);
     if (prev != ctx->device) (void)hipSetDevice(prev);
     if (e != hipSuccess) return rsr::hip_error(ctx, e, "rsr_eval_unknown_noalloc launch");
     return RSR_OK;

@@ -185,8 +185,7 @@ struct rsr_plan {
     uint64_t* d_casc_counters = nullptr;
     uint32_t* d_casc_state = nullptr;  // persistent cascade state (zeroed per launch)
     int64_t casc_state_words = 0;
-    int32_t* d_list = nullptr;
-    uint64_t* d_list_counter = nullptr;
+    void* d_list = nullptr;  // SampleList
     hipStream_t cap = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -285,12 +284,10 @@ hipError_t enqueue_rest(const rsr_plan* p, int si, hipStream_t st) {
     const Segment& s = p->segs[si];
     const rsr::SegSrc src = seg_src(p, s, si);
     const int nj = static_cast<int>(s.jobs.size());
-    hipError_t e = rsr::launch_fill_u64(st, p->d_list_counter, 1, 0);
+    const rsr::SampleList list(p->d_list);
+    hipError_t e = rsr::launch_label(st, src, list);
     if (e == hipSuccess)
-        e = rsr::launch_label(st, src, p->d_list, p->d_list_counter, p->ctx->cu_count * 16);
-    if (e == hipSuccess)
-        e = rsr::launch_bfs(st, s.sys, src, p->d_list, p->d_list_counter, RSR_UNKNOWN_ONLY, nullptr,
-                            p->ctx->cu_count * 8);
+        e = rsr::launch_eval(st, s.sys, src, list, RSR_UNKNOWN_ONLY, nullptr, p->ctx->cu_count);
     if (e == hipSuccess && s.any_grad)
         e = rsr::launch_grad(st, s.n, s.K, nullptr, nullptr, nullptr, s.max_N, p->d_grad_part,
                              nullptr, nullptr, p->d_jobs + s.first_pos, nj);
@@ -462,7 +459,7 @@ void free_plan(rsr_plan* p) {
     if (p->cap) (void)hipStreamDestroy(p->cap);
     void* dev[] = {p->d_jobs, p->d_offsets, p->d_counts, p->d_count_part, p->d_grad_part,
                    p->d_casc_words, p->d_casc_index, p->d_casc_counters, p->d_casc_state,
-                   p->d_list, p->d_list_counter};
+                   p->d_list};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     if (p->h_counts) (void)hipHostFree(p->h_counts);
@@ -625,8 +622,7 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
                 sizeof(uint32_t) * static_cast<size_t>((state_words + 1) / 2 * 2));
     dmalloc(reinterpret_cast<void**>(&p->d_casc_counters),
             sizeof(uint64_t) * rsr::CascadeBuffers::kCounterU64);
-    dmalloc(reinterpret_cast<void**>(&p->d_list), sizeof(int32_t) * max_total);
-    dmalloc(reinterpret_cast<void**>(&p->d_list_counter), sizeof(uint64_t) * 2);
+    dmalloc(&p->d_list, rsr::SampleList::bytes(max_total));
     dmalloc(reinterpret_cast<void**>(&p->d_G_all), sizeof(float) * p->G_total);
     if (e == hipSuccess)
         e = rsr::host_malloc(&p->h_counts, sizeof(uint64_t) * (8 * n_jobs + 1));

@@ -1,0 +1,105 @@
+"""Evaluation of the system function 64 samples at a time, where it can go
+wrong: ragged sample and edge counts, parallel edges and self-loops, graphs
+made of ears (rings, chains of rings, ladders), the switch from a block to a
+wave per group, graphs with few waves per block, upper planes, unaligned
+flags, and the list of unclassified samples across its regions.  Everything is
+compared with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2604_17066_amd as R
+from helpers import unpack_states
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(name, rng):
+    if name == "ring":
+        n = 23
+        eu, ev = np.arange(n), (np.arange(n) + 1) % n
+    elif name == "rings":        # rings joined at nodes, and one bridge in the middle
+        eu, ev, at = [], [], 0
+        for k, size in enumerate((3, 5, 2, 7, 4)):
+            ring = [at] + list(range(at + 1, at + size))
+            eu += ring
+            ev += ring[1:] + [at]
+            at += size - 1
+            if k == 2:
+                eu.append(at)
+                ev.append(at + 1)
+                at += 1
+        n = at + 1
+    elif name == "ladder":
+        m = 20
+        eu = list(range(m - 1)) + list(range(m, 2 * m - 1)) + list(range(m))
+        ev = list(range(1, m)) + list(range(m + 1, 2 * m)) + list(range(m, 2 * m))
+        n = 2 * m
+    elif name == "multigraph":   # parallel edges, self-loops, 97 edges on 30 nodes
+        n = 30
+        eu = np.concatenate([np.arange(1, n), rng.integers(0, n, 68)])
+        ev = np.concatenate([[int(rng.integers(0, v)) for v in range(1, n)], rng.integers(0, n, 68)])
+    elif name == "pair":         # two nodes, two edges
+        n, eu, ev = 2, [0, 1], [1, 0]
+    else:                        # "large": few waves per block
+        n, m = 900, 2400
+        eu = np.concatenate([np.arange(1, n), rng.integers(0, n, m - n + 1)])
+        ev = np.concatenate([[int(rng.integers(max(0, v - 9), v)) for v in range(1, n)],
+                             rng.integers(0, n, m - n + 1)])
+    return {"n_nodes": int(n), "edge_u": np.asarray(eu, np.int32), "edge_v": np.asarray(ev, np.int32),
+            "source": 0, "sink": int(n) - 1}
+
+
+CASES = [("ring", 2, 0.97, 1), ("ring", 3, 0.97, 63), ("rings", 2, 0.96, 4000),
+         ("ladder", 2, 0.93, 4097), ("multigraph", 2, 0.9, 70_001), ("multigraph", 3, 0.9, 65),
+         ("pair", 2, 0.6, 129), ("large", 2, 0.98, 400)]
+
+
+@pytest.mark.parametrize("name,K,up,N", CASES)
+def test_every_sample(rsr_ctx, name, K, up, N):
+    rng = np.random.default_rng(N)
+    g = _graph(name, rng)
+    n = g["edge_u"].size
+    p = np.full((n, K), (1 - up) / (K - 1))
+    p[:, K - 1] = up
+    model = R.Model(rsr_ctx, p)
+    xs = R.rsr_sample(rsr_ctx, model, 8, 0, 0, N)
+    x = unpack_states(xs.cpu().numpy(), n, K)
+    for level in range(1, K):
+        sys = R.System(rsr_ctx, g, K=K, level=level, kind="st")
+        got = R.rsr_eval_unknown(rsr_ctx, sys, xs, N, None, which=R.RSR_ALL).cpu().numpy()
+        want, _ = oracle.eval_unknown(g, x, None, which=1, level=level)
+        np.testing.assert_array_equal(got, want, err_msg=f"st level {level}")
+    for level in (1, 2):
+        sys = R.System(rsr_ctx, g, K=K, level=level, kind="global")
+        got = R.rsr_eval_unknown(rsr_ctx, sys, xs, N, None, which=R.RSR_ALL).cpu().numpy()
+        want, _ = oracle.eval_unknown_global(g, x, None, which=1, level=level)
+        np.testing.assert_array_equal(got, want, err_msg=f"global level {level}")
+
+
+# Listed samples: none, few (a block per group), many (a wave per group), and
+# more tiles of flags than regions (N > 512 * 1024).
+@pytest.mark.parametrize("N,share,offset", [(1000, 0.0, 0), (1023, 0.05, 1), (4096, 1.0, 0),
+                                            (70_003, 0.6, 3), (540_001, 0.02, 2)])
+def test_listed_samples(rsr_ctx, N, share, offset):
+    rng = np.random.default_rng(N)
+    g = _graph("multigraph", rng)
+    n = g["edge_u"].size
+    model = R.Model(rsr_ctx, np.tile([[0.15, 0.85]], (n, 1)))
+    xs = R.rsr_sample(rsr_ctx, model, 9, 0, 0, N)
+    flags = np.where(rng.random(N) < share, 0, rng.integers(1, 4, N)).astype(np.uint8)
+    d = torch.zeros(N + 8, dtype=torch.uint8, device=rsr_ctx.device)
+    d[offset:offset + N] = torch.from_numpy(flags).to(rsr_ctx.device)
+    out = torch.full((N + 8,), 77, dtype=torch.uint8, device=rsr_ctx.device)
+    n_eval = torch.zeros(1, dtype=torch.int64, device=rsr_ctx.device)
+    x = unpack_states(xs.cpu().numpy(), n, 2)
+    for kind, ref in (("st", oracle.eval_unknown), ("global", oracle.eval_unknown_global)):
+        sys = R.System(rsr_ctx, g, level=1, kind=kind)
+        R.rsr_eval_unknown(rsr_ctx, sys, xs, N, d[offset:offset + N], Y=out[offset:offset + N],
+                           n_evaluated=n_eval)
+        got = out.cpu().numpy()
+        want, _ = ref(g, x, flags)
+        np.testing.assert_array_equal(got[offset:offset + N], want, err_msg=kind)
+        assert (got[:offset] == 77).all() and (got[offset + N:] == 77).all()
+        assert int(n_eval) == int((flags == 0).sum())
