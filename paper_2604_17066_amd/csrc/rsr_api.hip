@@ -587,11 +587,11 @@ static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* 
     std::vector<uint32_t> lo_off, up_off;
     slices(R_L, lo_weight, lo_off);
     slices(R_U, up_weight, up_off);
-    const bool sparse =
-        (R_L == 0 || lo_weight[0] > 0) && (R_U == 0 || up_weight[0] > 0) &&
-        256.0 * (static_cast<double>(lo_off.back()) + up_off.back()) <=
-            rsr::kSparseDensity * n * (K - 1) * 64.0 *
-                static_cast<double>(lo_off.size() + up_off.size() - 2);
+    const double density =
+        256.0 * (static_cast<double>(lo_off.back()) + up_off.back()) /
+        std::max(1.0, 64.0 * n * (K - 1) * static_cast<double>(lo_off.size() + up_off.size() - 2));
+    const bool sparse = (R_L == 0 || lo_weight[0] > 0) && (R_U == 0 || up_weight[0] > 0) &&
+                        density <= rsr::kSparseDensity;
     std::vector<uint16_t> lo_idx, up_idx;
     auto columns = [&](const std::vector<uint32_t>& rows, int64_t R, const std::vector<uint32_t>& off,
                        std::vector<uint16_t>& idx) {
@@ -645,6 +645,8 @@ static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* 
     part(&refs->d_upper_bits, up);
     if (sparse) {
         refs->sparse = true;
+        refs->sparse_count = density <= rsr::kSparseCountDensity &&
+                             std::max(R_L, R_U) >= rsr::kSparseCountRows;
         part(&refs->d_lower_off, lo_off);
         part(&refs->d_lower_idx, lo_idx);
         part(&refs->d_upper_off, up_off);
@@ -846,8 +848,14 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
                     "the persistent cascade takes LABEL mode on consistent rows, N <= 2^31-1");
     uint32_t* match = mode == RSR_COUNT ? d_match : nullptr;
     // RSR_AUTO: for LABEL on consistent rows (each sample stops at its first
-    // match) the sparse form, or the cascade for dense rows; otherwise the FP4 matrix-core form, which makes the
-    // most tests per second in both modes; popcount beyond 1280 bits.
+    // match) the sparse form, or the cascade for dense rows; otherwise the
+    // sparse count for many sparse rows, else the FP4 matrix-core form, which
+    // makes the most tests per second in both modes; popcount beyond 1280 bits.
+    if (form == RSR_AUTO && refs->sparse_count && (mode == RSR_COUNT || !refs->consistent)) {
+        RSR_HIP(ctx, rsr::launch_sparse_count(ctx->stream, refs, d_samples, N, mode, ctx->cu_count,
+                                              d_flags, match));
+        return RSR_OK;
+    }
     if (form == RSR_AUTO && refs->KS4 > 0 && (mode == RSR_COUNT || !refs->consistent))
         form = RSR_MFMA_FP4;
     const bool matrix = form == RSR_MFMA || form == RSR_MFMA_FP4;

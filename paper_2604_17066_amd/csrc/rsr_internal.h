@@ -156,6 +156,7 @@ struct rsr_refs {
     // first chunk of slice s.  Absent (sparse false) when a row has no bit or
     // the rows are too dense (kSparseDensity).
     bool sparse = false;
+    bool sparse_count = false;            // for counting too (kSparseCount...)
     uint32_t* d_lower_off = nullptr;      // [ceil(R_L/64) + 1]
     uint16_t* d_lower_idx = nullptr;      // columns of NOT t(r)
     uint32_t* d_upper_off = nullptr;      // [ceil(R_U/64) + 1]
@@ -274,6 +275,14 @@ __device__ __forceinline__ uint8_t* seg_Y(const SegSrc& s, int j) {
 // 512 / 603 and 1712 / 1498.
 constexpr double kSparseDensity = 0.6;
 
+// The same for counting every match, where a sample does not stop at its first
+// one, and the rows of the longer side from which it pays: writing out the
+// counts takes about 50 us per tile whatever the rows.  1e6 samples of 295 bits,
+// 4000 rows per side, sparse against FP4: 290 to 350 / 830 us; 40 bits and 300
+// rows per side 124 / 41, 2e4 samples of 295 bits and 200 rows 21 / 12.
+constexpr double kSparseCountDensity = 0.3;
+constexpr int64_t kSparseCountRows = 2048;
+
 // Most blocks of a launch of the sparse form (k_sparse.hip), each with an
 // output region of its own.
 constexpr int kSparseRegions = 512;
@@ -376,6 +385,10 @@ hipError_t launch_dom_cascade(hipStream_t st, const rsr_refs* refs, const SegSrc
 // samples of the largest job.
 hipError_t launch_dom_sparse(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
                              int64_t max_N, const CascadeBuffers& cb, int cus);
+// Every row against every sample with sparse operands: COUNT, or LABEL on rows
+// that are not a consistent set.
+hipError_t launch_sparse_count(hipStream_t st, const rsr_refs* refs, const uint32_t* d_samples,
+                               int64_t N, int mode, int cus, uint8_t* d_flags, uint32_t* d_match);
 // `cus` (the device's CU count) picks the sample tiles per wave for the grid.
 hipError_t launch_dom_mfma(hipStream_t st, const rsr_refs* refs, const uint32_t* d_samples,
                            int64_t N, int mode, bool fp4, int cus, uint8_t* d_flags,

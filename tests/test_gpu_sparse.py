@@ -136,3 +136,43 @@ def test_jobs_of_a_plan(rsr_ctx, sizes):
                 want = R.rsr_classify(rsr_ctx, refs, b.samples, job["N"], form=R.RSR_POPCOUNT)
                 np.testing.assert_array_equal(b.flags.cpu().numpy(), want.cpu().numpy())
         plan.close()
+
+
+# Match counts: more matches per lane than a flush holds (255), rows past whole
+# slices, empty sides, more tiles than CUs, ragged ends.
+@pytest.mark.parametrize("n,K,R_L,R_U,N,bits,mode", [
+    (20, 2, 1, 2048, 1, 2, R.RSR_COUNT),
+    (33, 2, 2049, 63, 129, 3, R.RSR_COUNT),
+    (64, 2, 0, 2100, 2049, 1, R.RSR_COUNT),
+    (64, 2, 9001, 0, 700, 1, R.RSR_COUNT),
+    (40, 3, 9001, 20_003, 3001, 1, R.RSR_COUNT),
+    (295, 2, 300, 2111, 40_001, 6, R.RSR_COUNT),
+    (1250, 2, 100, 2050, 1500, 5, R.RSR_COUNT),
+    (4096, 2, 2060, 65, 500, 5, R.RSR_COUNT),
+    (20, 2, 65, 63, 129, 3, R.RSR_COUNT),
+    (33, 2, 2065, 63, 5000, 3, R.RSR_LABEL),
+    (70, 4, 300, 5000, 4097, 2, R.RSR_LABEL),
+])
+def test_counts_against_the_oracle(rsr_ctx, n, K, R_L, R_U, N, bits, mode):
+    """Rows of no system: both sides match the same samples."""
+    rng = np.random.default_rng(n + N + bits)
+    lower = np.where(rng.random((R_L, n)) < bits / n, rng.integers(0, K, (R_L, n)), K - 1)
+    upper = np.where(rng.random((R_U, n)) < bits / n, rng.integers(0, K, (R_U, n)), 0)
+    lower[:, 1], upper[:, 0] = K - 2, 1      # no row without a bit
+    lower, upper = lower.astype(np.uint8), upper.astype(np.uint8)
+    model = R.Model(rsr_ctx, np.full((n, K), 1.0 / K))
+    refs = R.Refs(rsr_ctx, n, K, lower, upper)
+    if mode == R.RSR_LABEL:
+        assert not refs.consistent
+    xs = R.rsr_sample(rsr_ctx, model, 31, 0, 0, N)
+    want, wl, wu = oracle.classify(lower, upper, unpack_states(xs.cpu().numpy(), n, K),
+                                   mode=1 if mode == R.RSR_COUNT else 0)
+    got = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode)
+    np.testing.assert_array_equal(got.cpu().numpy(), want)
+    if mode == R.RSR_COUNT:
+        flags, match = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, want_match=True)
+        np.testing.assert_array_equal(flags.cpu().numpy(), want)
+        np.testing.assert_array_equal(match.cpu().numpy()[:, 0], wl)
+        np.testing.assert_array_equal(match.cpu().numpy()[:, 1], wu)
+        if R_U > 20_000:
+            assert int(match[:, 1].max()) > 255 * 16 * 4
