@@ -35,12 +35,10 @@ __device__ __forceinline__ uint32_t other_end(uint32_t uv, uint32_t w) {
     return u == w ? v : u;
 }
 
-// Grows `set` over the usable edges until nothing changes or `stop` (a node,
-// or -1 for none) is marked; returns whether `stop` is marked.  With parent
-// (and depth) not null, records the marking edge (and depth) of every newly
-// marked node.
-__device__ inline bool grow(uint32_t* set, uint64_t usable, const uint32_t* __restrict__ s_edges,
-                            int stop, uint16_t* parent, uint16_t* depth) {
+// Grows `set` over the usable edges until nothing changes, recording the
+// marking edge and the depth of every newly marked node.
+__device__ inline void grow(uint32_t* set, uint64_t usable, const uint32_t* __restrict__ s_edges,
+                            uint16_t* parent, uint16_t* depth) {
     const int lane = threadIdx.x & 63;
     while (true) {
         bool changed = false;
@@ -54,15 +52,14 @@ __device__ inline bool grow(uint32_t* set, uint64_t usable, const uint32_t* __re
             const uint32_t ru = bit(set, u), rv = bit(set, v);
             if (ru != rv) {
                 const uint32_t w = ru ? v : u;
-                if (parent) parent[w] = static_cast<uint16_t>(e);
-                if (depth) depth[w] = static_cast<uint16_t>(depth[ru ? u : v] + 1);
+                parent[w] = static_cast<uint16_t>(e);
+                depth[w] = static_cast<uint16_t>(depth[ru ? u : v] + 1);
                 atomicOr(&set[w >> 5], 1u << (w & 31));
                 changed = true;
             }
         }
         wave_sync();
-        if (stop >= 0 && __builtin_amdgcn_readfirstlane(static_cast<int>(bit(set, stop)))) return true;
-        if (!__any(changed)) return false;
+        if (!__any(changed)) return;
     }
 }
 
@@ -74,7 +71,7 @@ __device__ inline int count(const uint32_t* set, int words) {
     return c;
 }
 
-// Per-wave LDS working set of the global-connectivity test.
+// Per-wave LDS working set of the two-edge-connectivity test.
 struct GlobalSets {
     uint32_t* reach;    // [node_words]
     uint32_t* covered;  // [edge_words]
@@ -98,16 +95,13 @@ __device__ __forceinline__ GlobalSets global_sets(uint32_t* base, int n_nodes, i
     return g;
 }
 
-// Global connectivity of the usable edges: S >= 1 when every node is reached
-// from node 0; S >= 2 when, in addition, no usable edge is a bridge.  A
-// spanning tree comes from the search (parents and depths); every usable
-// non-tree edge (u, v) closes a cycle with the tree path from u to v, and the
-// tree edges on no such cycle are exactly the bridges.  Wave-uniform result.
-// With keep_tree, the parents of the spanning tree are recorded at level 1
-// too (they are always recorded at level 2).
-__device__ inline bool global_at_least(uint64_t usable, int level,
-                                       const uint32_t* __restrict__ s_edges, int n_edges,
-                                       int n_nodes, const GlobalSets& g, bool keep_tree = false) {
+// Whether the usable edges connect all nodes and none of them is a bridge.  A
+// spanning tree comes from a search from node 0 (parents and depths); every
+// usable non-tree edge (u, v) closes a cycle with the tree path from u to v,
+// and the tree edges on no such cycle are exactly the bridges.  Wave-uniform
+// result.
+__device__ inline bool two_edge_connected(uint64_t usable, const uint32_t* __restrict__ s_edges,
+                                          int n_edges, int n_nodes, const GlobalSets& g) {
     const int lane = threadIdx.x & 63;
     const int node_words = (n_nodes + 31) >> 5, edge_words = (n_edges + 31) >> 5;
     fill(g.reach, node_words, 0u);
@@ -118,10 +112,8 @@ __device__ inline bool global_at_least(uint64_t usable, int level,
         g.depth[0] = 0;
     }
     wave_sync();
-    const bool tree = level >= 2 || keep_tree;
-    grow(g.reach, usable, s_edges, -1, tree ? g.parent : nullptr, tree ? g.depth : nullptr);
+    grow(g.reach, usable, s_edges, g.parent, g.depth);
     if (count(g.reach, node_words) < n_nodes) return false;
-    if (level < 2) return true;
     fill(g.covered, edge_words, 0u);
     wave_sync();
     uint64_t todo = usable;

@@ -524,7 +524,7 @@ __global__ __launch_bounds__(kWideBlock) void k_global2_wide(
                 usable |= static_cast<uint64_t>((word >> (e & 31)) & 1u) << k;
             }
         }
-        const bool up = graph::global_at_least(usable, 2, s_edges, n_edges, n_nodes, g);
+        const bool up = graph::two_edge_connected(usable, s_edges, n_edges, n_nodes, g);
         if (lane == 0) seg_Y(seg, job)[h] = up ? 1 : 0;
         graph::wave_sync();
     }
