@@ -144,7 +144,8 @@ void compute_thresholds(int32_t n, int32_t K, const double* p, uint64_t* C) {
 // kernels themselves (upper rows as samples against the lower rows): the FP4
 // form when the handle has matrix-core operands (0.72 against 7.15 ms for the
 // popcount form at 2.5e4 rows of 590 bits per side; its 2.5e4 samples fill a
-// fifth of the CUs), else the popcount form.  Synchronous.
+// fifth of the CUs), else the popcount form.  Synchronous.  Callers that know the
+// rows to be consistent skip it.
 rsr_status check_consistency(rsr_ctx* ctx, rsr_refs* refs, const std::vector<uint32_t>& up) {
     refs->consistent = true;
     if (refs->R_L == 0 || refs->R_U == 0) return RSR_OK;
@@ -431,81 +432,95 @@ rsr_status rsr_model_destroy(rsr_model* m) {
 
 namespace rsr {
 
-static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
-                             const uint8_t* upper, int64_t R_U, bool matrix_operands,
-                             rsr_refs** out) {
-    if (!ctx || !out) return RSR_EINVAL;
-    *out = nullptr;
+void pack_rows(int n, int K, const uint8_t* rows, int64_t R, bool complement,
+               std::vector<uint32_t>& bits) {
+    constexpr uint64_t kOnes = 0x0101010101010101ull, kTop = 0x8080808080808080ull;
+    const int PW = plane_words(n), W = sample_words(n, K), WR = dom_row_words(W);
+    const size_t at = bits.size();
+    bits.resize(at + static_cast<size_t>(R) * WR, 0u);
+    for (int64_t r = 0; r < R; ++r) {
+        const uint8_t* row = rows + r * n;
+        uint32_t* dst = bits.data() + at + r * WR;
+        // Eight components at a time: adding 128 - j to a byte sets its top
+        // bit when the state is at least j (states are below 128), and a
+        // product gathers the eight top bits.
+        for (int i = 0; i < n; i += 8) {
+            uint64_t x = 0;
+            std::memcpy(&x, row + i, static_cast<size_t>(std::min(8, n - i)));
+            for (int j = 1; j < K; ++j) {
+                const uint64_t ge = ((x + kOnes * static_cast<uint64_t>(128 - j)) & kTop) >> 7;
+                dst[(j - 1) * PW + i / 32] |=
+                    static_cast<uint32_t>((ge * 0x0102040810204080ull) >> 56) << (i % 32);
+            }
+        }
+        if (complement)  // within the planes' valid bits
+            for (int w = 0; w < W; ++w) {
+                const int valid = n - 32 * (w % PW);
+                dst[w] = ~dst[w] & (valid >= 32 ? ~0u : (1u << valid) - 1u);
+            }
+    }
+}
+
+rsr_status pack_refs(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
+                     const uint8_t* upper, int64_t R_U, std::vector<uint32_t>& lo,
+                     std::vector<uint32_t>& up) {
     if (n <= 0 || K < 2) return fail(ctx, RSR_EINVAL, "n must be > 0 and K >= 2");
     if (K > RSR_MAX_K || static_cast<int64_t>(n) * (K - 1) > RSR_MAX_BITS)
         return fail(ctx, RSR_EUNSUPPORTED, "n*(K-1) exceeds RSR_MAX_BITS or K > RSR_MAX_K");
     if (R_L < 0 || R_U < 0) return fail(ctx, RSR_EINVAL, "negative row count");
     if ((R_L > 0 && !lower) || (R_U > 0 && !upper))
         return fail(ctx, RSR_EINVAL, "NULL reference rows with a non-zero count");
+    // Whether every state is below K, eight at a time.
+    auto states_ok = [K](const uint8_t* v, int64_t count) {
+        constexpr uint64_t kOnes = 0x0101010101010101ull, kTop = 0x8080808080808080ull;
+        uint64_t bad = 0;
+        int64_t i = 0;
+        for (; i + 8 <= count; i += 8) {
+            uint64_t x;
+            std::memcpy(&x, v + i, 8);
+            bad |= x | ((x & ~kTop) + kOnes * static_cast<uint64_t>(128 - K));
+        }
+        for (; i < count; ++i) bad |= v[i] >= K ? kTop : 0;
+        return (bad & kTop) == 0;
+    };
+    if (!states_ok(lower, R_L * n)) return fail(ctx, RSR_EINVAL, "lower reference state >= K");
+    if (!states_ok(upper, R_U * n)) return fail(ctx, RSR_EINVAL, "upper reference state >= K");
+    if (dom_row_words(sample_words(n, K)) < 0)
+        return fail(ctx, RSR_EUNSUPPORTED, "packed width not supported");
+    pack_rows(n, K, lower, R_L, true, lo);
+    pack_rows(n, K, upper, R_U, false, up);
+    return RSR_OK;
+}
+
+static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, std::vector<uint32_t> lo,
+                             std::vector<uint32_t> up, bool matrix_operands, bool consistent,
+                             rsr_refs** out) {
     const int PW = plane_words(n);
     const int W = sample_words(n, K);
     const int WR = rsr::dom_row_words(W);
-    // Valid-bit mask per packed word (pad bits of each plane are 0).
-    std::vector<uint32_t> valid(W, 0u);
-    for (int j = 1; j < K; ++j)
-        for (int i = 0; i < n; ++i) valid[(j - 1) * PW + i / 32] |= 1u << (i % 32);
-    // Packs rows (complemented or not) into thermometer words, eight
-    // components at a time: adding 128 - j to a byte sets its top bit when the
-    // state is at least j (states are below 128), and a product gathers the
-    // eight top bits.  False on a state >= K.
-    auto pack = [&](const uint8_t* rows, int64_t R, bool complement, std::vector<uint32_t>& out) {
-        constexpr uint64_t kOnes = 0x0101010101010101ull, kTop = 0x8080808080808080ull;
-        for (int64_t r = 0; r < R; ++r) {
-            const uint8_t* row = rows + r * n;
-            uint32_t* dst = out.data() + r * WR;
-            for (int i = 0; i < n; i += 8) {
-                uint64_t x = 0;
-                std::memcpy(&x, row + i, static_cast<size_t>(std::min(8, n - i)));
-                if ((x | (x + kOnes * static_cast<uint64_t>(128 - K))) & kTop) return false;
-                for (int j = 1; j < K; ++j) {
-                    const uint64_t ge = ((x + kOnes * static_cast<uint64_t>(128 - j)) & kTop) >> 7;
-                    dst[(j - 1) * PW + i / 32] |=
-                        static_cast<uint32_t>((ge * 0x0102040810204080ull) >> 56) << (i % 32);
-                }
-            }
-            if (complement)
-                for (int w = 0; w < W; ++w) dst[w] = ~dst[w] & valid[w];
-        }
-        return true;
-    };
-    if (WR < 0) {
-        auto bad = [K](uint8_t v) { return v >= K; };
-        if (std::any_of(lower, lower + R_L * n, bad))
-            return fail(ctx, RSR_EINVAL, "lower reference state >= K");
-        if (std::any_of(upper, upper + R_U * n, bad))
-            return fail(ctx, RSR_EINVAL, "upper reference state >= K");
-        return fail(ctx, RSR_EUNSUPPORTED, "packed width not supported");
-    }
-    std::vector<uint32_t> lo(static_cast<size_t>(R_L) * WR, 0u), up(static_cast<size_t>(R_U) * WR, 0u);
-    if (!pack(lower, R_L, true, lo)) return fail(ctx, RSR_EINVAL, "lower reference state >= K");
-    if (!pack(upper, R_U, false, up)) return fail(ctx, RSR_EINVAL, "upper reference state >= K");
+    const int64_t R_L = static_cast<int64_t>(lo.size() / WR);
+    const int64_t R_U = static_cast<int64_t>(up.size() / WR);
     DeviceGuard g(ctx->device);
     // Store rows by increasing number of violation bits (stable): a row with
     // fewer constrained components dominates a larger region, so the LABEL
     // forms find most matches among the first rows.  Results do not depend
     // on the order.
     auto sort_rows = [&](std::vector<uint32_t>& rows, int64_t R, std::vector<int>& weight) {
-        std::vector<int64_t> order(R);
         std::vector<int> of(R);
+        std::vector<int64_t> next(static_cast<size_t>(W) * 32 + 2, 0);
         for (int64_t r = 0; r < R; ++r) {
-            order[r] = r;
             int c = 0;
             for (int w = 0; w < W; ++w) c += __builtin_popcount(rows[r * WR + w]);
             of[r] = c;
+            next[c + 1] += 1;
         }
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int64_t a, int64_t b) { return of[a] < of[b]; });
+        for (size_t c = 1; c < next.size(); ++c) next[c] += next[c - 1];
         std::vector<uint32_t> sorted(rows.size());
         weight.resize(R);
         for (int64_t r = 0; r < R; ++r) {
-            std::copy(rows.begin() + order[r] * WR, rows.begin() + (order[r] + 1) * WR,
-                      sorted.begin() + r * WR);
-            weight[r] = of[order[r]];
+            const int64_t to = next[of[r]]++;
+            std::copy(rows.begin() + r * WR, rows.begin() + (r + 1) * WR, sorted.begin() + to * WR);
+            weight[to] = of[r];
         }
         rows.swap(sorted);
     };
@@ -680,19 +695,18 @@ static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* 
         }
         if (e != hipSuccess) return hip_fail(ctx, e, "rsr_refs_create upload");
     }
-    rsr_status st = check_consistency(ctx, refs.get(), up);
-    if (st != RSR_OK) return st;
+    refs->consistent = true;
+    if (!consistent) {
+        rsr_status st = check_consistency(ctx, refs.get(), up);
+        if (st != RSR_OK) return st;
+    }
     *out = refs.release();
     return RSR_OK;
 }
 
-rsr_status refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
-                       const uint8_t* upper, int64_t R_U, bool matrix_operands, rsr_refs** out) {
-    try {
-        return build_refs(ctx, n, K, lower, R_L, upper, R_U, matrix_operands, out);
-    } catch (const std::bad_alloc&) {
-        return fail(ctx, RSR_ENOMEM, "host allocation");
-    }
+rsr_status refs_from_packed(rsr_ctx* ctx, int32_t n, int32_t K, const std::vector<uint32_t>& lower,
+                            const std::vector<uint32_t>& upper, bool consistent, rsr_refs** out) {
+    return build_refs(ctx, n, K, lower, upper, false, consistent, out);
 }
 
 }  // namespace rsr
@@ -707,7 +721,16 @@ rsr_status rsr_refs_consistent(const rsr_refs* refs, int32_t* out) {
 
 rsr_status rsr_refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
                            const uint8_t* upper, int64_t R_U, rsr_refs** out) {
-    return rsr::refs_create(ctx, n, K, lower, R_L, upper, R_U, true, out);
+    if (!ctx || !out) return RSR_EINVAL;
+    *out = nullptr;
+    try {
+        std::vector<uint32_t> lo, up;
+        rsr_status st = rsr::pack_refs(ctx, n, K, lower, R_L, upper, R_U, lo, up);
+        if (st != RSR_OK) return st;
+        return rsr::build_refs(ctx, n, K, std::move(lo), std::move(up), true, false, out);
+    } catch (const std::bad_alloc&) {
+        return fail(ctx, RSR_ENOMEM, "host allocation");
+    }
 }
 
 rsr_status rsr_refs_destroy(rsr_refs* refs) {

