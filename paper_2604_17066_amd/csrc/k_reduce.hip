@@ -6,15 +6,20 @@
 //
 // k_counts: one pass over flags (and Y) with per-thread counters, wavefront
 // and block reductions, one partial row per block; k_counts_final adds rows.
-// k_counts_vec: the same for one job in one launch, 16 flags per load; the
-// last block to finish (one ticket atomic per block) adds the rows.
+// k_counts_vec: the same in one launch, 16 flags per load; the last block to
+// finish (one ticket atomic per block) adds the rows.
+// k_counts_jobs: the counts of every job of a table, added into the job's
+// totals with one atomic per block and count.
 //
 // k_grad_bits: a[j][i] = #{h : Y_h = 1 and x_{h,i} >= j} for every thermometer
 // bit (plane j, component i).  Block column y = packed word w; each thread
 // walks a strided run of samples (about 64), counts the 32 bit positions of
 // its Y-masked words in bit-sliced form and then in 32 plain counters; the
 // block reduces them to one partial row.  Blocks in column 0 also count
-// #{Y = 1}.
+// #{Y = 1}.  With a job table a further column takes the jobs' counts: they
+// need no launch of their own, and hide behind the columns' sample words.  (48
+// jobs in three segments, 240 components: 610 us a run; 643 with launches for
+// counts, their sums and the gathered gradients, and three copies back.)
 // k_grad_finalize: c[i][s] = a[s][i] - a[s+1][i] (a[0][i] = #{Y = 1},
 // a[K][i] = 0), G[i][s] = (float)c / ((float)N * p[i][s]).
 #include "rsr_internal.h"
@@ -55,17 +60,8 @@ __global__ __launch_bounds__(kBlock) void k_fill_u64(unsigned long long* p, int6
 
 __global__ __launch_bounds__(kBlock) void k_counts(const uint8_t* __restrict__ flags,
                                                    const uint8_t* __restrict__ Y, int64_t N,
-                                                   unsigned long long* __restrict__ partial,
-                                                   const JobDev* __restrict__ jobs) {
-    // partial[job][block][0..4] = this block's n_L, n_U, n_u, n_both, n_u_up;
-    // with a job table, blockIdx.y selects the job.
-    if (jobs) {
-        const JobDev& jd = jobs[blockIdx.y];
-        flags = jd.flags;
-        Y = jd.Y;
-        N = jd.N;
-        partial += static_cast<int64_t>(blockIdx.y) * gridDim.x * 8;
-    }
+                                                   unsigned long long* __restrict__ partial) {
+    // partial[block][0..4] = this block's n_L, n_U, n_u, n_both, n_u_up.
     uint32_t nL = 0, nU = 0, nu = 0, nb = 0, nuu = 0;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
     for (int64_t h = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; h < N; h += stride) {
@@ -113,6 +109,60 @@ __device__ __forceinline__ void count_word(uint32_t w, uint32_t y, uint32_t (&c)
     c[4] += __popc(unk & ynz);
 }
 
+// One thread's share (samples or 16-sample chunks first, first + stride, ...)
+// of the counts of N samples: 16 bytes a load where both arrays are aligned.
+__device__ __forceinline__ void count_flags(const uint8_t* __restrict__ flags,
+                                            const uint8_t* __restrict__ Y, int64_t N,
+                                            int64_t first, int64_t stride, uint32_t (&c)[5]) {
+    const bool wide = ((reinterpret_cast<uintptr_t>(flags) | reinterpret_cast<uintptr_t>(Y)) & 15u) == 0;
+    const int64_t chunks = wide ? N >> 4 : 0;
+    for (int64_t k = first; k < chunks; k += stride) {
+        const uint4 f = reinterpret_cast<const uint4*>(flags)[k];
+        const uint4 y = Y ? reinterpret_cast<const uint4*>(Y)[k] : make_uint4(0, 0, 0, 0);
+        count_word(f.x, y.x, c);
+        count_word(f.y, y.y, c);
+        count_word(f.z, y.z, c);
+        count_word(f.w, y.w, c);
+    }
+    for (int64_t h = (chunks << 4) + first; h < N; h += stride) {
+        const uint32_t f = flags[h];
+        const uint32_t lo = f & 1u, up = (f >> 1) & 1u, unk = (lo | up) ^ 1u;
+        c[0] += lo;
+        c[1] += up & (lo ^ 1u);
+        c[2] += unk;
+        c[3] += lo & up;
+        c[4] += (unk && Y && Y[h]) ? 1u : 0u;
+    }
+}
+
+// A job's share of a block (block `block` of `blocks`) of the counts, added
+// into totals[0..4].
+__device__ __forceinline__ void add_job_counts(const JobDev& jd, int block, int blocks,
+                                               unsigned long long* __restrict__ totals) {
+    uint32_t c[5] = {0, 0, 0, 0, 0};
+    count_flags(jd.flags, jd.Y, jd.N, static_cast<int64_t>(block) * kBlock + threadIdx.x,
+                static_cast<int64_t>(blocks) * kBlock, c);
+    __shared__ uint32_t red[kBlock / 64][5];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const uint32_t v = wave_sum32(c[k]);
+        if (lane == 0) red[wave][k] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+        unsigned long long v = 0;
+        for (int w = 0; w < kBlock / 64; ++w) v += red[w][threadIdx.x];
+        if (v) atomicAdd(&totals[threadIdx.x], v);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_counts_jobs(const JobDev* __restrict__ jobs,
+                                                        unsigned long long* __restrict__ totals) {
+    add_job_counts(jobs[blockIdx.y], blockIdx.x, gridDim.x,
+                   totals + static_cast<int64_t>(blockIdx.y) * 8);
+}
+
 // The counts of k_counts for one job in one launch: 16 flags (and Y bytes)
 // per 16-byte load (both arrays 16-byte aligned), per-block partials, and the
 // last block to finish (a ticket counter, left at zero again) adds them into
@@ -128,27 +178,8 @@ __global__ __launch_bounds__(kBlock) void k_counts_vec(const uint8_t* __restrict
                                                        const unsigned long long* __restrict__ carry,
                                                        unsigned long long seq) {
     uint32_t c[5] = {0, 0, 0, 0, 0};
-    const int64_t chunks = N >> 4;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-    for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < chunks;
-         k += stride) {
-        const uint4 f = reinterpret_cast<const uint4*>(flags)[k];
-        const uint4 y = Y ? reinterpret_cast<const uint4*>(Y)[k] : make_uint4(0, 0, 0, 0);
-        count_word(f.x, y.x, c);
-        count_word(f.y, y.y, c);
-        count_word(f.z, y.z, c);
-        count_word(f.w, y.w, c);
-    }
-    if (blockIdx.x == 0)
-        for (int64_t h = (chunks << 4) + threadIdx.x; h < N; h += kBlock) {
-            const uint32_t f = flags[h];
-            const uint32_t lo = f & 1u, up = (f >> 1) & 1u, unk = (lo | up) ^ 1u;
-            c[0] += lo;
-            c[1] += up & (lo ^ 1u);
-            c[2] += unk;
-            c[3] += lo & up;
-            c[4] += (unk && Y && Y[h]) ? 1u : 0u;
-        }
+    count_flags(flags, Y, N, static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x,
+                static_cast<int64_t>(gridDim.x) * kBlock, c);
     __shared__ uint32_t red[kBlock / 64][5];
     __shared__ bool is_last;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -200,12 +231,10 @@ __global__ __launch_bounds__(kBlock) void k_counts_vec(const uint8_t* __restrict
         __hip_atomic_store(&out[6], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Sums the per-block partials of k_counts into out[0..4] (one block per job).
+// Sums the per-block partials of k_counts into out[0..4] (one block).
 __global__ __launch_bounds__(kBlock) void k_counts_final(const unsigned long long* __restrict__ partial,
                                                          int blocks,
                                                          unsigned long long* __restrict__ out) {
-    partial += static_cast<int64_t>(blockIdx.x) * blocks * 8;
-    out += static_cast<int64_t>(blockIdx.x) * 8;
     __shared__ unsigned long long red[kBlock / 64][5];
     unsigned long long v[5] = {0, 0, 0, 0, 0};
     for (int b = threadIdx.x; b < blocks; b += kBlock)
@@ -261,17 +290,23 @@ __device__ __forceinline__ void add_batch(uint32_t (&s)[kSliceBits], const uint3
 // Per-bit masked counts of one packed word column, written as per-block
 // partials: partial[(w * gridDim.x + bx) * 32 + b]; column 0 blocks also write
 // #{Y = 1} to ypart[bx].  Each thread takes samples h0, h0 + stride, ...
-// (coalesced across the wave).
+// (coalesced across the wave).  With a job table, column W adds the jobs' counts
+// into totals[job][8].
 __global__ __launch_bounds__(kBlock) void k_grad_bits(const uint32_t* __restrict__ xs,
                                                       const uint8_t* __restrict__ Y, int64_t N,
                                                       uint32_t* __restrict__ partial,
                                                       uint32_t* __restrict__ ypart,
                                                       const JobDev* __restrict__ jobs,
-                                                      int64_t job_stride) {
+                                                      int64_t job_stride, int W,
+                                                      unsigned long long* __restrict__ totals) {
     // With a job table, blockIdx.z selects the job; its partials start at
     // job * job_stride (u32).
     if (jobs) {
         const JobDev& jd = jobs[blockIdx.z];
+        if (static_cast<int>(blockIdx.y) == W) {
+            add_job_counts(jd, blockIdx.x, gridDim.x, totals + static_cast<int64_t>(blockIdx.z) * 8);
+            return;
+        }
         xs = jd.samples;
         Y = jd.Y;
         N = jd.N;
@@ -399,7 +434,8 @@ __global__ __launch_bounds__(kBlock) void k_grad_finalize(const uint32_t* __rest
                                                           float* __restrict__ G,
                                                           unsigned long long* __restrict__ counts,
                                                           const JobDev* __restrict__ jobs,
-                                                          int64_t job_stride) {
+                                                          int64_t job_stride,
+                                                          float* __restrict__ gathered) {
     if (jobs) {
         const JobDev& jd = jobs[blockIdx.y];
         p = jd.p;
@@ -409,6 +445,7 @@ __global__ __launch_bounds__(kBlock) void k_grad_finalize(const uint32_t* __rest
         partial += static_cast<int64_t>(blockIdx.y) * job_stride;
         ypart += static_cast<int64_t>(blockIdx.y) * job_stride;
         if (!G) return;
+        gathered += jd.g_off;
     }
     // One wavefront per (i, s); its lanes add the per-block partials.
     const int lane = threadIdx.x & 63;
@@ -432,6 +469,7 @@ __global__ __launch_bounds__(kBlock) void k_grad_finalize(const uint32_t* __rest
         const float pv = p[idx];
         const float g = pv > 0.0f ? static_cast<float>(cnt) / (static_cast<float>(N) * pv) : 0.0f;
         G[idx] = g;
+        if (gathered) gathered[idx] = g;
         if (counts) counts[idx] = cnt;
     }
 }
@@ -463,22 +501,7 @@ __global__ __launch_bounds__(kBlock) void k_importance_finalize(
     }
 }
 
-// Copies every job's gradient into one buffer (out + job.g_off), so a plan
-// returns all gradients with a single device-to-host copy.
-__global__ __launch_bounds__(kBlock) void k_gather_G(const JobDev* __restrict__ jobs, int nK,
-                                                     float* __restrict__ out) {
-    const JobDev& jd = jobs[blockIdx.y];
-    const int idx = blockIdx.x * kBlock + threadIdx.x;
-    if (idx < nK && jd.G) out[jd.g_off + idx] = jd.G[idx];
-}
-
 }  // namespace
-
-hipError_t launch_gather_G(hipStream_t st, const JobDev* jobs, int n_jobs, int nK, float* out) {
-    hipLaunchKernelGGL(k_gather_G, dim3((nK + kBlock - 1) / kBlock, n_jobs), dim3(kBlock), 0, st,
-                       jobs, nK, out);
-    return hipGetLastError();
-}
 
 hipError_t launch_fill_u64(hipStream_t st, uint64_t* p, int64_t count, uint64_t value) {
     const dim3 grid(static_cast<unsigned>((count + kBlock - 1) / kBlock));
@@ -488,20 +511,29 @@ hipError_t launch_fill_u64(hipStream_t st, uint64_t* p, int64_t count, uint64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_counts(hipStream_t st, const uint8_t* d_flags, const uint8_t* d_Y, int64_t N,
-                         uint64_t* d_counters, uint64_t* d_partial, const JobDev* jobs,
-                         int n_jobs) {
+static int64_t counts_blocks(int64_t N) {
     int64_t blocks = (N + kBlock * 16 - 1) / (kBlock * 16);
     if (blocks > kMaxReduceBlocks) blocks = kMaxReduceBlocks;
-    if (blocks < 1) blocks = 1;
-    const int nj = jobs ? n_jobs : 1;
-    hipLaunchKernelGGL(k_counts, dim3(static_cast<unsigned>(blocks), nj), dim3(kBlock), 0, st,
-                       d_flags, d_Y, N, reinterpret_cast<unsigned long long*>(d_partial), jobs);
+    return blocks < 1 ? 1 : blocks;
+}
+
+hipError_t launch_counts(hipStream_t st, const uint8_t* d_flags, const uint8_t* d_Y, int64_t N,
+                         uint64_t* d_counters, uint64_t* d_partial) {
+    const int64_t blocks = counts_blocks(N);
+    hipLaunchKernelGGL(k_counts, dim3(static_cast<unsigned>(blocks)), dim3(kBlock), 0, st, d_flags,
+                       d_Y, N, reinterpret_cast<unsigned long long*>(d_partial));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_counts_final, dim3(nj), dim3(kBlock), 0, st,
+    hipLaunchKernelGGL(k_counts_final, dim3(1), dim3(kBlock), 0, st,
                        reinterpret_cast<const unsigned long long*>(d_partial),
                        static_cast<int>(blocks), reinterpret_cast<unsigned long long*>(d_counters));
+    return hipGetLastError();
+}
+
+hipError_t launch_counts_jobs(hipStream_t st, const JobDev* jobs, int n_jobs, int64_t max_N,
+                              uint64_t* d_totals) {
+    hipLaunchKernelGGL(k_counts_jobs, dim3(static_cast<unsigned>(counts_blocks(max_N)), n_jobs),
+                       dim3(kBlock), 0, st, jobs, reinterpret_cast<unsigned long long*>(d_totals));
     return hipGetLastError();
 }
 
@@ -525,7 +557,7 @@ hipError_t launch_importance(hipStream_t st, int n, const double* d_p64, const u
     const int64_t bx = grad_blocks(N);
     uint32_t* ypart = d_partial + static_cast<int64_t>(W) * bx * 32;
     hipLaunchKernelGGL(k_grad_bits, dim3(static_cast<unsigned>(bx), W, 1), dim3(kBlock), 0, st,
-                       d_samples, d_Y, N, d_partial, ypart, nullptr, int64_t{0});
+                       d_samples, d_Y, N, d_partial, ypart, nullptr, int64_t{0}, W, nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int waves_per_block = kBlock / 64;
@@ -543,26 +575,43 @@ int64_t grad_blocks(int64_t N) {
     return bx;
 }
 
-hipError_t launch_grad(hipStream_t st, int n, int K, const float* d_p, const uint32_t* d_samples,
-                       const uint8_t* d_Y, int64_t N, uint32_t* d_partial, float* d_G,
-                       uint64_t* d_counts, const JobDev* jobs, int n_jobs) {
+// k_grad_bits and k_grad_finalize of one job, or of the jobs of a table.
+static hipError_t grad_launches(hipStream_t st, int n, int K, const float* d_p,
+                                const uint32_t* d_samples, const uint8_t* d_Y, int64_t N,
+                                uint32_t* d_partial, float* d_G, uint64_t* d_counts,
+                                const JobDev* jobs, int n_jobs, uint64_t* d_totals,
+                                float* d_gathered) {
     const int PW = plane_words(n);
     const int W = (K - 1) * PW;
     const int64_t bx = grad_blocks(N);
     const int64_t job_stride = static_cast<int64_t>(W) * bx * 32 + bx;
-    const int nj = jobs ? n_jobs : 1;
     uint32_t* ypart = d_partial + static_cast<int64_t>(W) * bx * 32;
-    hipLaunchKernelGGL(k_grad_bits, dim3(static_cast<unsigned>(bx), W, nj), dim3(kBlock), 0, st,
-                       d_samples, d_Y, N, d_partial, ypart, jobs, job_stride);
+    hipLaunchKernelGGL(k_grad_bits, dim3(static_cast<unsigned>(bx), jobs ? W + 1 : W, n_jobs),
+                       dim3(kBlock), 0, st, d_samples, d_Y, N, d_partial, ypart, jobs, job_stride, W,
+                       reinterpret_cast<unsigned long long*>(d_totals));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int total = n * K;
     const int waves_per_block = kBlock / 64;
-    hipLaunchKernelGGL(k_grad_finalize, dim3((total + waves_per_block - 1) / waves_per_block, nj),
+    hipLaunchKernelGGL(k_grad_finalize, dim3((total + waves_per_block - 1) / waves_per_block, n_jobs),
                        dim3(kBlock), 0, st,
                        d_partial, ypart, static_cast<int>(bx), d_p, n, K, PW, N, d_G,
-                       reinterpret_cast<unsigned long long*>(d_counts), jobs, job_stride);
+                       reinterpret_cast<unsigned long long*>(d_counts), jobs, job_stride, d_gathered);
     return hipGetLastError();
+}
+
+hipError_t launch_grad(hipStream_t st, int n, int K, const float* d_p, const uint32_t* d_samples,
+                       const uint8_t* d_Y, int64_t N, uint32_t* d_partial, float* d_G,
+                       uint64_t* d_counts) {
+    return grad_launches(st, n, K, d_p, d_samples, d_Y, N, d_partial, d_G, d_counts, nullptr, 1,
+                         nullptr, nullptr);
+}
+
+hipError_t launch_grad_jobs(hipStream_t st, int n, int K, const JobDev* jobs, int n_jobs,
+                            int64_t max_N, uint32_t* d_partial, uint64_t* d_totals,
+                            float* d_gathered) {
+    return grad_launches(st, n, K, nullptr, nullptr, nullptr, max_N, d_partial, nullptr, nullptr,
+                         jobs, n_jobs, d_totals, d_gathered);
 }
 
 }  // namespace rsr

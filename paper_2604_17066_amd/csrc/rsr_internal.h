@@ -465,13 +465,12 @@ hipError_t launch_pick(hipStream_t st, const uint8_t* d_flags, int64_t N, int64_
 hipError_t launch_boundary(hipStream_t st, const rsr_system* sys, const uint32_t* xs, int64_t N,
                            const int64_t* d_pick, int64_t n_pick, uint8_t* d_rows,
                            uint8_t* d_side, int grid_cap);
-// With a job table (jobs != nullptr) the reductions run once per job in one
-// launch; N must then be the largest job size (it sizes the grid), counters
-// receive [n_jobs][8] and the gradient partials need n_jobs * (W * bx * 32 +
-// bx) u32 with bx = grad_blocks(N).
 hipError_t launch_counts(hipStream_t st, const uint8_t* d_flags, const uint8_t* d_Y, int64_t N,
-                         uint64_t* d_counters, uint64_t* d_partial, const JobDev* jobs = nullptr,
-                         int n_jobs = 1);
+                         uint64_t* d_counters, uint64_t* d_partial);
+// The counts of a table's jobs (the largest of max_N samples), added into
+// d_totals[n_jobs][8].
+hipError_t launch_counts_jobs(hipStream_t st, const JobDev* jobs, int n_jobs, int64_t max_N,
+                              uint64_t* d_totals);
 // One job's counts in one launch (flags and Y 16-byte aligned); d_ticket is a
 // zero-initialised u32 the kernel leaves at zero.
 // out[0..4] = n_L, n_U, n_u, n_both, n_u_up and out[5] = *d_carry (0 when
@@ -481,10 +480,16 @@ hipError_t launch_counts_vec(hipStream_t st, const uint8_t* d_flags, const uint8
                              uint64_t* out, uint64_t* d_partial, uint32_t* d_ticket,
                              const uint64_t* d_carry, uint64_t seq);
 int64_t grad_blocks(int64_t N);
+// d_partial: W * bx * 32 + bx u32 with bx = grad_blocks(N).
 hipError_t launch_grad(hipStream_t st, int n, int K, const float* d_p, const uint32_t* d_samples,
                        const uint8_t* d_Y, int64_t N, uint32_t* d_partial, float* d_G,
-                       uint64_t* d_counts, const JobDev* jobs = nullptr, int n_jobs = 1);
-hipError_t launch_gather_G(hipStream_t st, const JobDev* jobs, int n_jobs, int nK, float* out);
+                       uint64_t* d_counts);
+// The gradients of a table's jobs, also written to d_gathered at the jobs'
+// g_off, and their counts as launch_counts_jobs; d_partial once per job, with
+// bx = grad_blocks(max_N).
+hipError_t launch_grad_jobs(hipStream_t st, int n, int K, const JobDev* jobs, int n_jobs,
+                            int64_t max_N, uint32_t* d_partial, uint64_t* d_totals,
+                            float* d_gathered);
 // Binary Birnbaum importance I[i] = c1 / (N p1) - c0 / (N p0), fp64 then
 // rounded to fp32 (k_reduce.hip); d_partial as for launch_grad.
 hipError_t launch_importance(hipStream_t st, int n, const double* d_p64, const uint32_t* d_samples,

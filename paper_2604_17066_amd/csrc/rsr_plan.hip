@@ -170,13 +170,15 @@ struct rsr_plan {
     rsr::JobDev* d_jobs = nullptr;
     int64_t* d_offsets = nullptr;  // per segment [jobs + 1], concatenated
     std::vector<int64_t> offset_base;
-    uint64_t* d_counts = nullptr;     // [jobs][8]
-    uint64_t* h_counts = nullptr;     // pinned [jobs][8]
-    float* d_G_all = nullptr;         // every job's gradient, gathered (job.g_off)
-    float* h_G_all = nullptr;         // pinned copy
+    // What a run returns, one block here and one pinned copy: counts [jobs][8],
+    // the persistent cascade's time-out flag, every job's gradient (job.g_off).
+    uint64_t* d_counts = nullptr;
+    uint64_t* h_counts = nullptr;
+    uint64_t* d_timeout = nullptr;    // in the block
+    float* d_G_all = nullptr;         // in the block
+    float* h_G_all = nullptr;         // in the copy
     int64_t G_total = 0;
     std::vector<int64_t> host_g_off;  // device position -> offset in the gather buffer
-    uint64_t* d_count_part = nullptr;
     uint32_t* d_grad_part = nullptr;
     uint32_t* d_casc_words = nullptr;
     int32_t* d_casc_index = nullptr;
@@ -248,15 +250,15 @@ hipError_t enqueue_classify(const rsr_plan* p, int si, hipStream_t st, Choice ch
     const Segment& s = p->segs[si];
     const rsr::SegSrc src = seg_src(p, s, si, n_jobs, total);
     if (choice == kPersist) {
-        // counters[15] is the barrier time-out flag, cleared once per run at
-        // the start of the graph and copied back with the counts.
+        // The barrier time-out flag is cleared once per run at the start of
+        // the graph and copied back with the counts.
         const rsr::CascadeBuffers cb = casc_buffers(p);
         hipError_t e = rsr::launch_fill_u64(st, reinterpret_cast<uint64_t*>(p->d_casc_state),
                                             (p->casc_state_words + 1) / 2, 0);
         if (e != hipSuccess) return e;
         return rsr::launch_casc_persist(st, s.refs, src, cb, rsr::mfma_head_shape(),
                                         p->d_casc_state,
-                                        reinterpret_cast<unsigned long long*>(p->d_casc_counters + 15),
+                                        reinterpret_cast<unsigned long long*>(p->d_timeout),
                                         p->ctx->cu_count);
     }
     if (choice == kSparse)
@@ -288,15 +290,11 @@ hipError_t enqueue_rest(const rsr_plan* p, int si, hipStream_t st) {
     hipError_t e = rsr::launch_label(st, src, list);
     if (e == hipSuccess)
         e = rsr::launch_eval(st, s.sys, src, list, RSR_UNKNOWN_ONLY, nullptr, p->ctx->cu_count);
-    if (e == hipSuccess && s.any_grad)
-        e = rsr::launch_grad(st, s.n, s.K, nullptr, nullptr, nullptr, s.max_N, p->d_grad_part,
-                             nullptr, nullptr, p->d_jobs + s.first_pos, nj);
-    if (e == hipSuccess && s.any_grad)
-        e = rsr::launch_gather_G(st, p->d_jobs + s.first_pos, nj, s.n * s.K, p->d_G_all);
+    uint64_t* totals = p->d_counts + static_cast<int64_t>(s.first_pos) * 8;
     if (e == hipSuccess)
-        e = rsr::launch_counts(st, nullptr, nullptr, s.max_N,
-                               p->d_counts + static_cast<int64_t>(s.first_pos) * 8,
-                               p->d_count_part, p->d_jobs + s.first_pos, nj);
+        e = s.any_grad ? rsr::launch_grad_jobs(st, s.n, s.K, p->d_jobs + s.first_pos, nj, s.max_N,
+                                               p->d_grad_part, totals, p->d_G_all)
+                       : rsr::launch_counts_jobs(st, p->d_jobs + s.first_pos, nj, s.max_N, totals);
     return e;
 }
 
@@ -457,14 +455,11 @@ void free_plan(rsr_plan* p) {
     if (p->exec) (void)hipGraphExecDestroy(p->exec);
     if (p->graph) (void)hipGraphDestroy(p->graph);
     if (p->cap) (void)hipStreamDestroy(p->cap);
-    void* dev[] = {p->d_jobs, p->d_offsets, p->d_counts, p->d_count_part, p->d_grad_part,
-                   p->d_casc_words, p->d_casc_index, p->d_casc_counters, p->d_casc_state,
-                   p->d_list};
+    void* dev[] = {p->d_jobs, p->d_offsets, p->d_counts, p->d_grad_part, p->d_casc_words,
+                   p->d_casc_index, p->d_casc_counters, p->d_casc_state, p->d_list};
     for (void* d : dev)
         if (d) (void)hipFree(d);
     if (p->h_counts) (void)hipHostFree(p->h_counts);
-    if (p->h_G_all) (void)hipHostFree(p->h_G_all);
-    if (p->d_G_all) (void)hipFree(p->d_G_all);
     delete p;
 }
 
@@ -548,7 +543,6 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
     std::vector<rsr::JobDev> host_jobs;
     std::vector<int64_t> host_offsets;
     int64_t max_total = 0, max_words = 0, max_grad = 0;
-    int max_jobs = 0;
     for (Segment& s : p->segs) {
         if (s.total > 0x7FFFFFFFll) {
             free_plan(p);
@@ -583,7 +577,6 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
         host_offsets.push_back(off);
         max_total = std::max(max_total, s.total);
         max_words = std::max(max_words, static_cast<int64_t>(s.W));
-        max_jobs = std::max(max_jobs, static_cast<int>(s.jobs.size()));
         const int64_t bx = rsr::grad_blocks(s.max_N);
         max_grad = std::max(max_grad, static_cast<int64_t>(s.jobs.size()) *
                                           (static_cast<int64_t>(s.W) * bx * 32 + bx));
@@ -610,9 +603,13 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
     };
     dmalloc(reinterpret_cast<void**>(&p->d_jobs), sizeof(rsr::JobDev) * host_jobs.size());
     dmalloc(reinterpret_cast<void**>(&p->d_offsets), sizeof(int64_t) * host_offsets.size());
-    dmalloc(reinterpret_cast<void**>(&p->d_counts), sizeof(uint64_t) * 8 * n_jobs);
-    dmalloc(reinterpret_cast<void**>(&p->d_count_part),
-            sizeof(uint64_t) * 8 * rsr::kMaxReduceBlocks * max_jobs);
+    const size_t counts_u64 = 8 * static_cast<size_t>(n_jobs) + 1;
+    const size_t result_bytes = sizeof(uint64_t) * counts_u64 + sizeof(float) * p->G_total;
+    dmalloc(reinterpret_cast<void**>(&p->d_counts), result_bytes);
+    if (e == hipSuccess) {
+        p->d_timeout = p->d_counts + counts_u64 - 1;
+        p->d_G_all = reinterpret_cast<float*>(p->d_counts + counts_u64);
+    }
     dmalloc(reinterpret_cast<void**>(&p->d_grad_part), sizeof(uint32_t) * max_grad);
     dmalloc(reinterpret_cast<void**>(&p->d_casc_words),
             sizeof(uint32_t) * 2 * static_cast<size_t>(max_words) * cap);
@@ -623,20 +620,17 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
     dmalloc(reinterpret_cast<void**>(&p->d_casc_counters),
             sizeof(uint64_t) * rsr::CascadeBuffers::kCounterU64);
     dmalloc(&p->d_list, rsr::SampleList::bytes(max_total));
-    dmalloc(reinterpret_cast<void**>(&p->d_G_all), sizeof(float) * p->G_total);
-    if (e == hipSuccess)
-        e = rsr::host_malloc(&p->h_counts, sizeof(uint64_t) * (8 * n_jobs + 1));
-    if (e == hipSuccess)
-        e = rsr::host_malloc(&p->h_G_all, sizeof(float) * (p->G_total + 1));
+    if (e == hipSuccess) e = rsr::host_malloc(&p->h_counts, result_bytes);
+    if (e == hipSuccess) p->h_G_all = reinterpret_cast<float*>(p->h_counts + counts_u64);
     if (e == hipSuccess)
         e = hipMemcpy(p->d_jobs, host_jobs.data(), sizeof(rsr::JobDev) * host_jobs.size(),
                       hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(p->d_offsets, host_offsets.data(), sizeof(int64_t) * host_offsets.size(),
                       hipMemcpyHostToDevice);
-    // The persistent cascade's time-out flag (counters[15]) must read 0 in
-    // the tuner's trials too.
-    if (e == hipSuccess) e = hipMemset(p->d_casc_counters, 0, sizeof(uint64_t) * 16);
+    // The persistent cascade's time-out flag must read 0 in the tuner's trials
+    // too.
+    if (e == hipSuccess) e = hipMemset(p->d_timeout, 0, sizeof(uint64_t));
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
     if (e != hipSuccess) {
         free_plan(p);
@@ -691,7 +685,8 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
     }
     // Record the whole plan.
     e = hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) e = rsr::launch_fill_u64(p->cap, p->d_casc_counters + 15, 1, 0);
+    if (e == hipSuccess)
+        e = rsr::launch_fill_u64(p->cap, p->d_counts, static_cast<int64_t>(counts_u64), 0);
     for (size_t si = 0; si < p->segs.size() && e == hipSuccess; ++si) {
         const Segment& s = p->segs[si];
         e = enqueue_sample(p, static_cast<int>(si), p->cap);
@@ -699,14 +694,7 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
         if (e == hipSuccess) e = enqueue_rest(p, static_cast<int>(si), p->cap);
     }
     if (e == hipSuccess)
-        e = hipMemcpyAsync(p->h_counts, p->d_counts, sizeof(uint64_t) * 8 * n_jobs,
-                           hipMemcpyDeviceToHost, p->cap);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(p->h_counts + 8 * static_cast<size_t>(n_jobs), p->d_casc_counters + 15,
-                           sizeof(uint64_t), hipMemcpyDeviceToHost, p->cap);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(p->h_G_all, p->d_G_all, sizeof(float) * p->G_total,
-                           hipMemcpyDeviceToHost, p->cap);
+        e = hipMemcpyAsync(p->h_counts, p->d_counts, result_bytes, hipMemcpyDeviceToHost, p->cap);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(p->cap, &graph);
     if (e == hipSuccess) e = e2;
