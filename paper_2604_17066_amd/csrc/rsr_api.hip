@@ -606,7 +606,7 @@ static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, std::vector<uin
         256.0 * (static_cast<double>(lo_off.back()) + up_off.back()) /
         std::max(1.0, 64.0 * n * (K - 1) * static_cast<double>(lo_off.size() + up_off.size() - 2));
     const bool sparse = (R_L == 0 || lo_weight[0] > 0) && (R_U == 0 || up_weight[0] > 0) &&
-                        density <= rsr::kSparseDensity;
+                        density <= rsr::sparse_density(n * (K - 1), std::max(R_L, R_U));
     std::vector<uint16_t> lo_idx, up_idx;
     auto columns = [&](const std::vector<uint32_t>& rows, int64_t R, const std::vector<uint32_t>& off,
                        std::vector<uint16_t>& idx) {

@@ -155,7 +155,7 @@ struct rsr_refs {
     // [chunk][64 rows][4], as many as its longest row takes; a shorter row
     // repeats its last column, the last slice its last row.  off[s] is the
     // first chunk of slice s.  Absent (sparse false) when a row has no bit or
-    // the rows are too dense (kSparseDensity).
+    // the rows are too dense (sparse_density).
     bool sparse = false;
     bool sparse_count = false;            // for counting too (kSparseCount...)
     uint32_t* d_lower_off = nullptr;      // [ceil(R_L/64) + 1]
@@ -270,18 +270,31 @@ __device__ __forceinline__ uint8_t* seg_Y(const SegSrc& s, int j) {
 
 // Share of the packed bits that the rows may have set (with the padding of
 // their chunks) for the sparse form to be the automatic LABEL form.  The
-// form's time follows the set bits, the cascade's does not: at 8000 rows per
-// side sparse against cascade, 295 bits and 1e6 samples 210 / 374 us at 0.3,
-// 466 / 633 at 0.5 and 1811 / 1849 at 0.8; 1250 bits and 2e5 samples 248 / 311,
-// 512 / 603 and 1712 / 1498.
-constexpr double kSparseDensity = 0.6;
+// form's time follows the set bits, the cascade's does not, so the line lies
+// where the samples that no row decides pay for all rows' bits.  us, sparse /
+// cascade:
+// * below kWideRows rows a side, at most kSparseSmallBits bits: 295 bits, 1e6
+//   samples, 12,000 rows 832 / 1016 at 0.35 and 1703 / 1954 at 0.55; 120 bits,
+//   3e5 samples 258 / 335 at 0.55;
+// * more bits (the columns of fewer samples fit the LDS): 1250 bits, 2e5
+//   samples, 8000 rows 1167 / 1586 at 0.3; 900 bits, 3000 rows 241 / 373 at
+//   0.3, 516 / 379 at 0.45;
+// * from kWideRows rows on, where the cascade grows its rounds faster: 295
+//   bits, 1e6 samples, 1e5 rows 4316 / 3272 at 0.4; 3e5 samples, 8e4 rows 852 /
+//   1330 at 0.2, 2938 / 1949 at 0.3; 900 bits, 1e5 samples, 6e4 rows 448 / 865
+//   at 0.15, 1628 / 1520 at 0.25.
+constexpr int kSparseSmallBits = 384;
+inline double sparse_density(int bits, int64_t rows);
 
 // The same for counting every match, where a sample does not stop at its first
 // one, and the rows of the longer side from which it pays: writing out the
 // counts takes about 50 us per tile whatever the rows.  1e6 samples of 295 bits,
 // 4000 rows per side, sparse against FP4: 290 to 350 / 830 us; 40 bits and 300
-// rows per side 124 / 41, 2e4 samples of 295 bits and 200 rows 21 / 12.
-constexpr double kSparseCountDensity = 0.3;
+// rows per side 124 / 41, 2e4 samples of 295 bits and 200 rows 21 / 12.  The
+// share of set bits: 295 bits, 3e5 samples, 8.8e4 rows 2154 / 3581 at 0.15 and
+// 4262 / 3637 at 0.25; 1250 bits, 1e5 samples, 4.4e4 rows 1504 / 2668 and
+// 2908 / 2671; 640 bits, 2e5 samples, 2.2e4 rows 695 / 1180 and 1284 / 1156.
+constexpr double kSparseCountDensity = 0.2;
 constexpr int64_t kSparseCountRows = 2048;
 
 // Most blocks of a launch of the sparse form (k_sparse.hip), each with an
@@ -371,6 +384,9 @@ inline CascadeShape mfma_wide_shape() {
 // 0.96 of mfma_tail_shape's; on graph2's 1e4 rows per side mfma_tail_shape is
 // the faster by 18%).
 constexpr int64_t kWideRows = 16384;
+inline double sparse_density(int bits, int64_t rows) {
+    return rows >= kWideRows ? 0.2 : bits <= kSparseSmallBits ? 0.6 : 0.3;
+}
 
 // Largest refs->KS (64-wide k-steps) of the matrix-core round 0.
 constexpr int kMaxHeadSteps = 10;

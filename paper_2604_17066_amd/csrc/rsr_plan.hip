@@ -6,8 +6,9 @@
 // probabilities, section 5, so every hazard scenario of one network shares
 // them).  Each stage of the hot path runs once per segment over the
 // concatenation of its jobs' samples, addressed by a global index with a job
-// offset table: one sampler launch, one classification cascade, one label and
-// one BFS launch, one gradient and one count launch with a job grid dimension.
+// offset table: one sampler launch, the classification's rounds, one label and
+// one evaluation launch, one launch for gradient and flag counts with a job grid
+// dimension and one that finishes the gradients.
 // Small jobs therefore fill the GPU together and the launch count is
 // O(segments), not O(jobs).  Before capture an autotuner times the candidate
 // classification configurations of each segment on its own data and keeps the
