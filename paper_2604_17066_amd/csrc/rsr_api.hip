@@ -313,7 +313,8 @@ rsr_status rsr_ctx_create(int device, void* hip_stream, rsr_ctx** out) {
         rsr::dev_malloc(&ctx->ws.casc_counters,
                         sizeof(uint64_t) * rsr::CascadeBuffers::kCounterU64) != hipSuccess ||
         rsr::dev_malloc(&ctx->ws.count_part, sizeof(uint64_t) * rsr::kMaxReduceBlocks * 8) != hipSuccess ||
-        rsr::dev_malloc(&ctx->ws.grad_part, sizeof(uint32_t) * (static_cast<size_t>(RSR_MAX_BITS) + 1) *
+        rsr::dev_malloc(&ctx->ws.grad_part, sizeof(uint32_t) *
+                                                (static_cast<size_t>(rsr::kMaxPaddedBits) + 1) *
                                                 rsr::kMaxGradBlocks) != hipSuccess ||
         rsr::host_malloc(&ctx->ws.host_counts, sizeof(uint64_t) * 16) != hipSuccess)
         st = RSR_ENOMEM;

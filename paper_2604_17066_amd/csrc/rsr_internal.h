@@ -22,6 +22,9 @@ int dom_row_words(int W);
 // Reduction shapes (k_reduce.hip): at most this many blocks write partials.
 constexpr int kMaxReduceBlocks = 1024;
 constexpr int kMaxGradBlocks = 64;
+// At most this many packed bits with the planes' padding: up to 31 bits in each
+// of RSR_MAX_K - 1 planes.
+constexpr int kMaxPaddedBits = RSR_MAX_BITS + 31 * (RSR_MAX_K - 1);
 // Largest k-step count of the matrix-core form (n (K-1) <= 1280 bits).
 constexpr int kMaxMfmaSteps = 20;   // int8 form: 64 k per step, 1280 bits
 constexpr int kMaxMfma4Steps = 10;  // FP4 form: 128 k per step, 1280 bits
@@ -84,7 +87,7 @@ struct Workspace {
     uint64_t* count_part = nullptr;    // [kMaxReduceBlocks][8] u64 partial counts
     void* list = nullptr;              // unknown-sample list (SampleList)
     int64_t list_cap = 0;
-    uint32_t* grad_part = nullptr;     // [RSR_MAX_BITS * kMaxGradBlocks + kMaxGradBlocks] u32
+    uint32_t* grad_part = nullptr;     // [(kMaxPaddedBits + 1) * kMaxGradBlocks] u32
     uint64_t* host_counts = nullptr;   // pinned, 16 u64
     uint64_t* host_counts_dev = nullptr;  // the device address of host_counts
     uint64_t estimate_seq = 0;         // last sequence number of rsr_estimate's counts
