@@ -201,7 +201,8 @@ def main():
     peaks = {"popcount": VALU_PEAK_OPS, "mfma": MFMA_I8_PEAK_OPS, "mfma_fp4": MFMA_FP4_PEAK_FLOPS}
     ops_per_test = {"popcount": W, "mfma": 2 * KP, "mfma_fp4": 2 * KP}
     # The roofline kernel is the COUNT-mode classification of the form the step
-    # uses; the automatic form classifies in COUNT mode with the FP4 form.
+    # uses; for the automatic form, which on sparse rows leaves out the bits that
+    # a row does not constrain, the exhaustive FP4 form.
     dom = args.form if args.form != "auto" else "mfma_fp4"
     count_ms = kern[dom]["count_ms"]
     achieved = kern[dom]["count_achieved"]

@@ -229,7 +229,7 @@ rsr_status rsr_sample(rsr_ctx* ctx, const rsr_model* model, uint64_t seed, uint3
  * operands 0 / +-1 and fp32 accumulation, exact because every partial sum
  * is a small integer), RSR_AUTO (for LABEL mode on consistent rows the
  * sparse form, which tests only the components that a row constrains, or the
- * cascade where the rows constrain most of them; else the sparse form for
+ * cascade where the rows constrain many of them; else the sparse form for
  * many rows, the FP4 form up to 1280 bits, or the popcount form),
  * RSR_PERSIST (the cascade with its rounds after round 0 in one persistent,
  * cooperative launch; its grid barriers wait with a time limit, and a
