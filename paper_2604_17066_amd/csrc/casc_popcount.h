@@ -22,10 +22,12 @@ __device__ __forceinline__ uint32_t andnot_or(uint32_t a, uint32_t b, uint32_t c
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0xAE);
 }
 
-// Rows per side staged in LDS at a time (at most 32 KB for both sides).
+// Rows per side staged in LDS at a time (at most 32 KB for both sides): a
+// multiple of 8, since the rows are tested in groups of 8, which would read past
+// a tile that ends inside one (96 words: 40 rows, not 42).
 template <int W>
 constexpr int tile_rows() {
-    return 4096 / W > 64 ? 64 : (4096 / W < 8 ? 8 : 4096 / W);
+    return 4096 / W > 64 ? 64 : (4096 / W < 8 ? 8 : 4096 / W / 8 * 8);
 }
 
 // Block-level: tests S samples per lane against rows [l0, l1) (lower) and
@@ -43,6 +45,7 @@ __device__ __forceinline__ void test_rows(const uint32_t (&x)[S][W], const bool 
                                           const uint32_t* __restrict__ up_b, int u0, int u1,
                                           uint32_t (&mnL)[S], uint32_t (&mnU)[S], uint32_t* lds) {
     constexpr int T = tile_rows<W>();
+    static_assert(T % 8 == 0, "whole groups of rows");
     const int nL = l1 - l0, nU = u1 - u0;
     const int n_max = nL > nU ? nL : nU;
     bool any_live = false;
