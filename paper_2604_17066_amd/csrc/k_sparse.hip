@@ -658,11 +658,15 @@ __global__ __launch_bounds__(kCountThreads, 4) void k_sparse_count(
     }
 }
 
-// LDS of a block with tiles of 128 << lg samples.
+// LDS of a block with tiles of 128 << lg samples.  In a list round the tile's
+// place also takes the survivors' numbers, two bytes a sample: more than the
+// columns of fewer than 16 bits.
 size_t lds_bytes(const rsr_refs* refs, int lg, bool first) {
-    const size_t tile = static_cast<size_t>(refs->n) * (refs->K - 1) << (lg + 4);
+    const size_t bits = static_cast<size_t>(refs->n) * (refs->K - 1);
     const size_t size = size_t{128} << lg;
-    return sizeof(TileMasks) + tile + (first ? 0 : 4 * (kThreads + size + refs->W * size));
+    if (first) return sizeof(TileMasks) + (bits << (lg + 4));
+    return sizeof(TileMasks) + ((bits < 16 ? 16 : bits) << (lg + 4)) +
+           4 * (kThreads + size + refs->W * size);
 }
 
 // Largest tile whose block shares a CU's 160 KB of LDS with another one.

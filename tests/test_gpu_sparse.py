@@ -95,6 +95,38 @@ def test_large_against_the_popcount_form(rsr_ctx, n, K, R_L, R_U, N):
     assert {1, 2} <= set(np.unique(got).tolist())
 
 
+@pytest.mark.parametrize("n,K,upper_side", [(5, 2, True), (7, 2, True), (8, 2, False), (15, 2, True),
+                                            (4, 3, True), (5, 4, False)])
+def test_few_bits_many_undecided(rsr_ctx, n, K, upper_side):
+    """A list of survivors that takes more room than the columns of its tile: fewer
+    than 16 bits, three rounds (more than 6144 rows), more undecided samples
+    (524288) than the smaller tiles hold, some of them decided in the last
+    round."""
+    N, top = 1_100_003, K - 1
+    first, later = [0, 1], [0, 2, 3]
+    if n >= 8:
+        first, later = [0, 1, 2], [0, 3, 4, 5]
+    far, near = (top, 0) if upper_side else (0, top)
+    rows = np.full((7000, n), near, dtype=np.uint8)
+    rows[:6200, first] = far
+    rows[6200:, later] = far
+    none = np.zeros((0, n), dtype=np.uint8)
+    refs = R.Refs(rsr_ctx, n, K, *((none, rows) if upper_side else (rows, none)))
+    p = np.full((n, K), 0.12)
+    p[:, near] = 0.0
+    p[:, near] = 1.0 - p.sum(axis=1)
+    model = R.Model(rsr_ctx, p)
+    xs, got = _flags(rsr_ctx, model, refs, 13, N)
+    x = unpack_states(xs.cpu().numpy(), n, K)
+
+    def hit(row):
+        return (x >= row).all(axis=1) if upper_side else (x <= row).all(axis=1)
+
+    early, late = hit(rows[0]), hit(rows[6200])
+    assert (~early).sum() > 600_000 and (late & ~early).sum() > 100
+    np.testing.assert_array_equal(got, np.where(early | late, 2 if upper_side else 1, 0))
+
+
 def test_rows_without_a_bit_and_dense_rows_keep_their_labels(rsr_ctx):
     rng = np.random.default_rng(3)
     n, N = 40, 5000
