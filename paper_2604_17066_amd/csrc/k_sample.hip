@@ -26,7 +26,12 @@
 //    instruction and would pull the uniform values into vector registers.
 //  * A dword of a block is the high halves of two neighbouring components, so
 //    packed 16-bit instructions compare both at once (classes2): three
-//    instructions per pair give "above" and "tie" as a two-bit field.
+//    instructions per pair give "above" and "tie" as a two-bit field.  Only a
+//    threshold below 2^16 (a state less likely than 1.5e-5) is not decided by
+//    its field 0, so such components come as a mask, and one of them that is
+//    not "above" redraws its block, 2 in 2^16 times.  (1e6 samples of 295
+//    components that fail with probability 1e-6: 65 us, 62 with 0.01; 247 where
+//    every sample redraws the blocks of such a word.)
 // Measured, against 20 products per block and one compare per component and
 // threshold: 1e6 samples of 295 two-state components 84 -> 67 us, of 295
 // three-state ones 114 -> 84 us; a plan's 48 jobs of 65536 samples of 240
@@ -164,7 +169,7 @@ __device__ __forceinline__ void for_uniform(uint32_t v, F f) {
 }
 
 // min(max(u - s, 0), 2) of both 16-bit halves: 0 below, 1 tie, 2 above (see
-// pack_thresholds in rsr_internal.h).
+// pack_threshold in rsr_internal.h).
 __device__ __forceinline__ uint32_t classes2(uint32_t u, uint32_t s) {
     const u16x2 d = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, u),
                                                   __builtin_bit_cast(u16x2, s));
@@ -234,7 +239,7 @@ __device__ __forceinline__ void draw_words(const uint64_t* __restrict__ thresh,
                     else B[s] |= e << (2 * (4 * (q & 1) + j));
                 }
         }
-        uint32_t acc[KM1], tie = 0, force = 0;
+        uint32_t acc[KM1], tie = 0, low = 0;
 #pragma unroll
         for (int s = 0; s < KM1; ++s) {
             // "Above" is the upper bit of a field: A's to the even bits, B's at
@@ -244,16 +249,17 @@ __device__ __forceinline__ void draw_words(const uint64_t* __restrict__ thresh,
             const uint32_t x = ((t >> 15) ^ t) & 0x0000AAAAu;
             acc[s] = (t ^ x ^ (x << 15)) | pw[s * kPackWords + 16];
             tie |= (A[s] & 0x55555555u) | ((B[s] & 0x55555555u) << 1);
-            force |= pw[s * kPackWords + 17];
+            low |= pw[s * kPackWords + 17] & ~acc[s];
         }
-        if (tie | force) {
+        if (tie | low) {
             // Tie bit 16 h + 8 (q mod 2) + 2 j + (q div 2): fold j and h.
             uint32_t f = tie | (tie >> 16);
             f |= f >> 4;
             f |= f >> 2;
-            const uint32_t blocks = (f & 1u) | ((f >> 7) & 2u) | ((f << 1) & 4u) | ((f >> 6) & 8u);
-            redraw_blocks<KM1>(thresh, n, wi * 32, force ? 15u : blocks, key0, key1, glo, ghi,
-                               stream, acc);
+            uint32_t blocks = (f & 1u) | ((f >> 7) & 2u) | ((f << 1) & 4u) | ((f >> 6) & 8u);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) blocks |= (low >> (8 * q)) & 0xFFu ? 1u << q : 0u;
+            redraw_blocks<KM1>(thresh, n, wi * 32, blocks, key0, key1, glo, ghi, stream, acc);
         }
 #pragma unroll
         for (int s = 0; s < KM1; ++s) out[static_cast<int64_t>(s * PW + wi) * N + h] = acc[s];

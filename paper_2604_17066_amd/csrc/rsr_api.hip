@@ -225,7 +225,7 @@ void fill_model_stage(const ModelLayout& L, int n, int K, const double* p, void*
                     i < n ? C[static_cast<size_t>(i) * (K - 1) + s] : uint64_t{1} << 32);
                 pw[k / 2] |= static_cast<uint32_t>(t.s) << (16 * (k % 2));
                 if (t.always) pw[16] |= 1u << k;
-                if (t.force) pw[17] = 1u;
+                if (t.low) pw[17] |= 1u << k;
             }
         }
     float* pf = reinterpret_cast<float*>(base + L.p32);

@@ -32,27 +32,25 @@ constexpr int kMaxMfma4Steps = 10;  // FP4 form: 128 k per step, 1280 bits
 // Sampler form of the thresholds of one packed word (32 components) and one
 // plane: 16 dwords of 16-bit thresholds (dword 4 q + j holds components 8 q +
 // 2 j in its low and 8 q + 2 j + 1 in its high half, the halves' positions in
-// Philox block q), the word's always-up components as a bit mask, and a flag
-// (nonzero: no component of the word may be decided from its high half).
+// Philox block q), and the word's always-up components and those of
+// PackedThreshold::low as bit masks.
 constexpr int kPackWords = 18;
 
 // The 16-bit threshold s of a threshold C in [0, 2^32], such that for the high
 // half u of a uniform word min(max(u - s, 0), 2) is 0 when the word is below
 // C, 2 when it is not, and 1 when the low half has to decide (or, harmlessly,
-// where it would not have to: that path compares the whole word).
+// where it would not have to: that path compares the whole word).  Below 2^16
+// (low) a 0 leaves the word open too: u = 0 would have to give 1, and no s does.
 struct PackedThreshold {
     uint16_t s;
-    bool always, force;
+    bool always, low;
 };
 inline PackedThreshold pack_threshold(uint64_t C) {
     const uint32_t high = static_cast<uint32_t>(C >> 16);
-    if (C == 0) return {65535, true, false};               // every word is at or above 0
-    if (high >= 65536) return {65535, false, false};       // none is at or above 2^32
-    if ((C & 0xFFFFu) == 0)                                // decided: u >= high
-        return high >= 2 ? PackedThreshold{static_cast<uint16_t>(high - 2), false, false}
-                         : PackedThreshold{65535, false, true};
-    return high >= 1 ? PackedThreshold{static_cast<uint16_t>(high - 1), false, false}
-                     : PackedThreshold{65535, false, true};
+    if (C == 0) return {65535, true, false};          // every word is at or above 0
+    if (high >= 65536) return {65535, false, false};  // none is at or above 2^32
+    if (high == 0) return {0, false, true};
+    return {static_cast<uint16_t>(high - 1), false, false};
 }
 
 // Every device and pinned-host allocation of the library goes through these
