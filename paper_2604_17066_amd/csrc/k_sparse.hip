@@ -50,7 +50,7 @@ constexpr int kThreads = 512;
 constexpr int kMinWaves = 4;  // per SIMD: two blocks in a CU
 constexpr int kWaves = kThreads / 64;
 static_assert(kSparseRegions <= kThreads, "a thread per region");
-constexpr int kMaxLg = 4;          // tiles of at most 2048 samples
+constexpr int kMaxLg = kSparseTiles - 1;  // tiles of at most 2048 samples
 constexpr int kMaxWords = 4 << kMaxLg;
 // Rows per side of round 0 (whole slices) and growth of the later rounds.  Round
 // 0 takes 4 us more for 256 rows than for 128 at 1e6 samples and saves that in
@@ -310,30 +310,46 @@ __device__ __forceinline__ uint32_t block_rank(uint32_t left, uint32_t* s_wave, 
     return rank;
 }
 
-// Round 0: every sample of the segment.  Tiles do not cross jobs: there are
-// `per_job` tiles in each, some of them empty where jobs differ in size.  A
-// block takes a range of tiles, whose samples are consecutive.
-__global__ __launch_bounds__(kThreads, kMinWaves) void k_sparse_first(SegSrc seg, int64_t per_job,
-                                                              SparseShape p, SparseRows low,
-                                                              SparseRows up, SparseList dst,
-                                                              int last) {
+// The job of tile t: the last one whose first tile is not behind it.  Every lane
+// of the wave must call it, with one t.
+__device__ __forceinline__ int job_of_tile(const int64_t* __restrict__ first_tile, int n_jobs,
+                                           int64_t t) {
+    int lo = 0, len = n_jobs;  // it is one of [lo, lo + len)
+    while (len > 1) {
+        const int step = (len + 63) >> 6, k = (threadIdx.x & 63) * step;
+        const uint64_t before = __ballot(k == 0 || (k < len && first_tile[lo + k] <= t));
+        const int at = (__popcll(before) - 1) * step;
+        lo += at;
+        len = min(step, len - at);
+    }
+    return lo;
+}
+
+// Round 0: every sample of the segment.  Tiles do not cross jobs; first_tile: see
+// JobTiles (unused without a job table).  A block takes a range of tiles, whose
+// samples are consecutive.
+__global__ __launch_bounds__(kThreads, kMinWaves) void k_sparse_first(
+    SegSrc seg, const int64_t* __restrict__ first_tile, int64_t tiles, SparseShape p,
+    SparseRows low, SparseRows up, SparseList dst, int last) {
     extern __shared__ uint4 lds4[];
     TileMasks& m = *reinterpret_cast<TileMasks*>(lds4);
     uint4* tile = lds4 + sizeof(TileMasks) / 16;
     const int tid = threadIdx.x, lg = p.lg, words = 4 << lg, size = 32 * words;
-    const int64_t tiles = per_job * (seg.jobs ? seg.n_jobs : 1);
     const int64_t per_block = (tiles + gridDim.x - 1) / gridDim.x;
-    int64_t region = -1;
+    const int64_t t_end = min(tiles, (blockIdx.x + 1) * per_block);
+    int64_t region = 0;
     uint32_t listed = 0;
-    for (int64_t t = blockIdx.x * per_block; t < min(tiles, (blockIdx.x + 1) * per_block); ++t) {
-        const int job = seg.jobs ? static_cast<int>(t / per_job) : 0;
-        const int64_t h0 = (t - job * per_job) << (7 + lg);
+    int64_t t = blockIdx.x * per_block;
+    int job = 0;
+    if (seg.jobs && t < t_end) job = job_of_tile(first_tile, seg.n_jobs, t);
+    for (bool begin = true; t < t_end; ++t, begin = false) {
+        if (seg.jobs && job + 1 < seg.n_jobs && first_tile[job + 1] <= t) ++job;
+        const int64_t h0 = (t - (seg.jobs ? first_tile[job] : 0)) << (7 + lg);
         const uint32_t* xs = global_ptr(seg.jobs ? seg.jobs[job].samples : seg.samples);
         uint8_t* flags = global_ptr(seg.jobs ? seg.jobs[job].flags : seg.flags);
         const int64_t N = seg.jobs ? seg.jobs[job].N : seg.N;
-        if (region < 0) region = (seg.jobs ? seg.offsets[job] : 0) + min(h0, N);
+        if (begin) region = (seg.jobs ? seg.offsets[job] : 0) + h0;
         const int count = static_cast<int>(min(static_cast<int64_t>(size), N - h0));
-        if (count <= 0) continue;  // block-uniform
         clear_masks(m, lg, count);
         load_columns(xs, N, h0, count, p, lg, reinterpret_cast<uint32_t*>(tile));
         __syncthreads();
@@ -361,8 +377,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void k_sparse_first(SegSrc seg
         __syncthreads();
     }
     if (!last && tid == 0)
-        dst.regions[blockIdx.x] = make_int2(static_cast<int>(max(region, int64_t{0})),
-                                            static_cast<int>(listed));
+        dst.regions[blockIdx.x] = make_int2(static_cast<int>(region), static_cast<int>(listed));
 }
 
 // A later round, on the listed samples.  The last round shares a tile's rows
@@ -704,9 +719,8 @@ hipError_t launch_sparse_count(hipStream_t st, const rsr_refs* refs, const uint3
 }
 
 hipError_t launch_dom_sparse(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
-                             int64_t max_N, const CascadeBuffers& cb, int cus) {
+                             const JobTiles& tiles, const CascadeBuffers& cb, int cus) {
     const int grid = 2 * cus < kSparseRegions ? 2 * cus : kSparseRegions;
-    const int64_t n_jobs = seg.jobs ? seg.n_jobs : 1;
     const int64_t rows = refs->R_L > refs->R_U ? refs->R_L : refs->R_U;
     int64_t lo = 0, hi = kFirst;
     SparseShape p{refs->W, plane_words(refs->n), refs->n, 0};
@@ -730,15 +744,17 @@ hipError_t launch_dom_sparse(hipStream_t st, const rsr_refs* refs, const SegSrc&
         };
         if (round == 0) {
             const int largest = largest_lg(refs, true);
-            int64_t per_job;
+            int64_t n_tiles;
             for (;; ++p.lg) {
-                per_job = (max_N + (128 << p.lg) - 1) >> (7 + p.lg);
-                if (p.lg == largest || per_job * n_jobs <= grid) break;
+                n_tiles = seg.jobs ? tiles.host[p.lg * tiles.stride + seg.n_jobs]
+                                   : (seg.total + (128 << p.lg) - 1) >> (7 + p.lg);
+                if (p.lg == largest || n_tiles <= grid) break;
             }
-            src_blocks = static_cast<int>(per_job * n_jobs < grid ? per_job * n_jobs : grid);
+            src_blocks = static_cast<int>(n_tiles < grid ? n_tiles : grid);
             hipLaunchKernelGGL(k_sparse_first, dim3(src_blocks), dim3(kThreads),
-                               lds_bytes(refs, p.lg, true), st, seg, per_job, p, low, up, list(0),
-                               last ? 1 : 0);
+                               lds_bytes(refs, p.lg, true), st, seg,
+                               seg.jobs ? tiles.dev + p.lg * tiles.stride : nullptr, n_tiles, p, low,
+                               up, list(0), last ? 1 : 0);
         } else {
             p.lg = largest_lg(refs, false);
             hipLaunchKernelGGL(k_sparse_list, dim3(grid), dim3(kThreads),

@@ -903,8 +903,8 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
         cb.set_counters(ctx->ws.casc_counters);
         if (form == RSR_AUTO && refs->sparse) {
             RSR_HIP(ctx, rsr::launch_dom_sparse(ctx->stream, refs,
-                                                rsr::single_src(d_samples, N, d_flags, nullptr), N,
-                                                cb, ctx->cu_count));
+                                                rsr::single_src(d_samples, N, d_flags, nullptr),
+                                                rsr::JobTiles(), cb, ctx->cu_count));
             return RSR_OK;
         }
         // The automatic form runs the rounds after round 0 in the FP4

@@ -302,6 +302,16 @@ constexpr int64_t kSparseCountRows = 2048;
 // output region of its own.
 constexpr int kSparseRegions = 512;
 
+// The sparse form takes a job's samples in tiles of 128 << lg, lg below
+// kSparseTiles.  first[lg * stride + j] = tiles of that size in the jobs before j
+// of a job table (j up to the number of jobs).
+constexpr int kSparseTiles = 5;
+struct JobTiles {
+    const int64_t* host = nullptr;
+    const int64_t* dev = nullptr;
+    int64_t stride = 0;
+};
+
 // Ping-pong buffers of the LABEL-mode cascade (k_dom_cascade): compacted
 // sample words [W][N] and original indices [N], plus one counter per round.
 struct CascadeBuffers {
@@ -399,10 +409,10 @@ hipError_t launch_dom_bits(hipStream_t st, const rsr_refs* refs, const uint32_t*
                            int64_t N, int mode, uint8_t* d_flags, uint32_t* d_match);
 hipError_t launch_dom_cascade(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
                               const CascadeBuffers& cb, const CascadeShape& shape, int grid_cap);
-// LABEL mode on a consistent reference set with sparse operands; max_N = the
-// samples of the largest job.
+// LABEL mode on a consistent reference set with sparse operands; tiles: only
+// with a job table.
 hipError_t launch_dom_sparse(hipStream_t st, const rsr_refs* refs, const SegSrc& seg,
-                             int64_t max_N, const CascadeBuffers& cb, int cus);
+                             const JobTiles& tiles, const CascadeBuffers& cb, int cus);
 // Every row against every sample with sparse operands: COUNT, or LABEL on rows
 // that are not a consistent set.
 hipError_t launch_sparse_count(hipStream_t st, const rsr_refs* refs, const uint32_t* d_samples,

@@ -169,7 +169,10 @@ struct rsr_plan {
     std::vector<int> pos;  // plan job index -> device position
     std::vector<Segment> segs;
     rsr::JobDev* d_jobs = nullptr;
-    int64_t* d_offsets = nullptr;  // per segment [jobs + 1], concatenated
+    // Per segment the jobs' offsets [jobs + 1] and their JobTiles
+    // [kSparseTiles][jobs + 1], concatenated.
+    std::vector<int64_t> offsets;
+    int64_t* d_offsets = nullptr;
     std::vector<int64_t> offset_base;
     // What a run returns, one block here and one pinned copy: counts [jobs][8],
     // the persistent cascade's time-out flag, every job's gradient (job.g_off).
@@ -262,8 +265,13 @@ hipError_t enqueue_classify(const rsr_plan* p, int si, hipStream_t st, Choice ch
                                         reinterpret_cast<unsigned long long*>(p->d_timeout),
                                         p->ctx->cu_count);
     }
-    if (choice == kSparse)
-        return rsr::launch_dom_sparse(st, s.refs, src, s.max_N, casc_buffers(p), p->ctx->cu_count);
+    if (choice == kSparse) {
+        const int64_t stride = static_cast<int64_t>(s.jobs.size()) + 1;
+        const int64_t at = p->offset_base[si] + stride;
+        return rsr::launch_dom_sparse(st, s.refs, src,
+                                      rsr::JobTiles{p->offsets.data() + at, p->d_offsets + at, stride},
+                                      casc_buffers(p), p->ctx->cu_count);
+    }
     if (choice == kCascade) {
         const rsr::CascadeBuffers cb = casc_buffers(p);
         hipError_t e = rsr::launch_fill_u64(st, cb.counters, rsr::CascadeBuffers::kMaxRounds, 0);
@@ -542,7 +550,7 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
     });
     p->pos.assign(n_jobs, 0);
     std::vector<rsr::JobDev> host_jobs;
-    std::vector<int64_t> host_offsets;
+    std::vector<int64_t>& host_offsets = p->offsets;
     int64_t max_total = 0, max_words = 0, max_grad = 0;
     for (Segment& s : p->segs) {
         if (s.total > 0x7FFFFFFFll) {
@@ -576,6 +584,14 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
             off += jb.N;
         }
         host_offsets.push_back(off);
+        for (int lg = 0; lg < rsr::kSparseTiles; ++lg) {
+            int64_t first = 0;
+            for (int j : s.jobs) {
+                host_offsets.push_back(first);
+                first += (jobs[j].N + (int64_t{128} << lg) - 1) >> (7 + lg);
+            }
+            host_offsets.push_back(first);
+        }
         max_total = std::max(max_total, s.total);
         max_words = std::max(max_words, static_cast<int64_t>(s.W));
         const int64_t bx = rsr::grad_blocks(s.max_N);

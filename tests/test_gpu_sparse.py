@@ -3,6 +3,8 @@ few components) where it can go wrong: tile, slice and round boundaries, ragged
 widths, more tiles than blocks, empty sides, unaligned flags and jobs of a
 plan whose sizes differ.  Small cases against the oracle, large ones against
 the popcount form."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -168,6 +170,61 @@ def test_jobs_of_a_plan(rsr_ctx, sizes):
                 want = R.rsr_classify(rsr_ctx, refs, b.samples, job["N"], form=R.RSR_POPCOUNT)
                 np.testing.assert_array_equal(b.flags.cpu().numpy(), want.cpu().numpy())
         plan.close()
+
+
+@pytest.mark.parametrize("sizes", [(200_001, 1, 2, 127, 128, 129, 3, 4097),
+                                   tuple([50] * 129 + [700_000]), tuple([700_000] + [50] * 129),
+                                   tuple([3] * 2100 + [400_000] + [130] * 2100)])
+def test_jobs_of_very_different_sizes(rsr_ctx, sizes):
+    """A block finds its job among up to 64, 64^2 and more; large jobs take more
+    than one tile a block, small ones less than one."""
+    n = 60
+    rng = np.random.default_rng(len(sizes))
+    g = {"n_nodes": n + 1, "edge_u": np.arange(n), "edge_v": np.arange(1, n + 1), "source": 0,
+         "sink": n}
+    lower, upper = _rows(rng, 900, 900, n, 2, 12)
+    refs = R.Refs(rsr_ctx, n, 2, lower, upper)
+    system = R.System(rsr_ctx, g)
+    model = R.Model(rsr_ctx, _model(n, 2, 12))
+    jobs = [{"model": model, "refs": refs, "system": system, "seed": 50 + k, "N": N, "grad": False,
+             "buffers": R.Buffers(rsr_ctx, n, 2, N)} for k, N in enumerate(sizes)]
+    plan = R.Plan(rsr_ctx, jobs, tune=False)
+    plan.run()
+    plan.results(want_grad=False)
+    for k, job in enumerate(jobs):
+        b = job["buffers"]
+        want = R.rsr_classify(rsr_ctx, refs, b.samples, job["N"], form=R.RSR_POPCOUNT)
+        assert torch.equal(b.flags, want), k
+    plan.close()
+
+
+def test_small_jobs_do_not_slow_a_large_one(rsr_ctx):
+    """One large job among 200 small ones against as many samples in one job: about
+    twice the time (the jobs' counts), not the many times that a range of tiles
+    padded to the largest job takes, whose few full ones fall to a few blocks."""
+    n = 240
+    rng = np.random.default_rng(8)
+    g = {"n_nodes": n + 1, "edge_u": np.arange(n), "edge_v": np.arange(1, n + 1), "source": 0,
+         "sink": n}
+    lower, upper = _rows(rng, 2000, 2000, n, 2, 12)
+    refs = R.Refs(rsr_ctx, n, 2, lower, upper)
+    system = R.System(rsr_ctx, g)
+    model = R.Model(rsr_ctx, _model(n, 2, 12))
+    ms = []
+    for sizes in ([1_100_000], [1_000_000] + [500] * 200):
+        jobs = [{"model": model, "refs": refs, "system": system, "seed": 50 + k, "N": N,
+                 "grad": False, "buffers": R.Buffers(rsr_ctx, n, 2, N)}
+                for k, N in enumerate(sizes)]
+        plan = R.Plan(rsr_ctx, jobs, tune=False)
+        best = float("inf")
+        for _ in range(5):
+            t = time.perf_counter()
+            plan.run()
+            plan.results(want_grad=False)
+            best = min(best, time.perf_counter() - t)
+        ms.append(best * 1e3)
+        plan.close()
+    assert ms[1] < 5 * ms[0], ms
 
 
 # Match counts: more matches per lane than a flush holds (255), rows past whole
