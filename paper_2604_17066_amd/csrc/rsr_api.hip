@@ -875,7 +875,9 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
     // match) the sparse form, or the cascade for dense rows; otherwise the
     // sparse count for many sparse rows, else the FP4 matrix-core form, which
     // makes the most tests per second in both modes; popcount beyond 1280 bits.
-    if (form == RSR_AUTO && refs->sparse_count && (mode == RSR_COUNT || !refs->consistent)) {
+    if (form == RSR_AUTO && refs->sparse_count && (mode == RSR_COUNT || !refs->consistent) &&
+        rsr::sparse_count_pays(mode, refs->n * (refs->K - 1), std::max(refs->R_L, refs->R_U), N,
+                               ctx->cu_count)) {
         RSR_HIP(ctx, rsr::launch_sparse_count(ctx->stream, refs, d_samples, N, mode, ctx->cu_count,
                                               d_flags, match));
         return RSR_OK;

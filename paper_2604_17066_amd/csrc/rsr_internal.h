@@ -288,15 +288,38 @@ constexpr int kSparseSmallBits = 384;
 inline double sparse_density(int bits, int64_t rows);
 
 // The same for counting every match, where a sample does not stop at its first
-// one, and the rows of the longer side from which it pays: writing out the
-// counts takes about 50 us per tile whatever the rows.  1e6 samples of 295 bits,
-// 4000 rows per side, sparse against FP4: 290 to 350 / 830 us; 40 bits and 300
-// rows per side 124 / 41, 2e4 samples of 295 bits and 200 rows 21 / 12.  The
-// share of set bits: 295 bits, 3e5 samples, 8.8e4 rows 2154 / 3581 at 0.15 and
-// 4262 / 3637 at 0.25; 1250 bits, 1e5 samples, 4.4e4 rows 1504 / 2668 and
-// 2908 / 2671; 640 bits, 2e5 samples, 2.2e4 rows 695 / 1180 and 1284 / 1156.
+// one: the share of set bits (295 bits, 3e5 samples, 8.8e4 rows 2154 / 3581 us
+// (FP4) at 0.15 and 4262 / 3637 at 0.25; 1250 bits, 1e5 samples, 4.4e4 rows
+// 1504 / 2668 and 2908 / 2671; 640 bits, 2e5 samples, 2.2e4 rows 695 / 1180 and
+// 1284 / 1156), and the fewest rows of the longer side.
 constexpr double kSparseCountDensity = 0.2;
 constexpr int64_t kSparseCountRows = 2048;
+
+// Whether it pays on sparse rows whose longer side has `rows`.  Writing out the
+// counts takes 50 to 100 us per tile, most where rows of a bit or two match
+// nearly everything, and a CU has a tile or two up to about 5e5 samples.  The
+// other form's time goes with the rows (30 ns each in COUNT) up to about 1e5
+// samples and grows from there.  Sparse / FP4, the worst over rows with 1 to 18
+// % of their bits set:
+// * COUNT: 8000 rows 0.94 (295 bits, 7e4 samples), 4000 rows of 640 bits 0.92,
+//   2048 of 1250 0.65, but 4000 of 295 1.52 and 2048 of 120 2.60; 1e6 samples:
+//   2048 rows of 120 to 1250 bits 0.47 to 0.97; up to a small tile a CU: 4000
+//   rows 0.77 to 1.04, 2048 of 295 1.36.
+// * LABEL on rows that are not consistent, where FP4 leaves a sample that is
+//   decided: 6200 rows of 900 bits 0.98, 1.2e4 of 640 0.71, 5.8e4 of 295 0.69,
+//   3200 of 1250 0.68, but 5000 of 900 1.15, 4000 of 640 1.21 and 1.7e4 of 295
+//   1.08; 1e6 samples: 2048 rows of 295 0.61, 4000 of 120 1.00, 4000 of 40 1.04;
+//   up to a small tile a CU: 8000 rows 0.26 to 1.09, 4000 of 295 1.41.
+// Beyond 1280 bits the popcount form takes 7 to 50 times as long.
+inline bool sparse_count_pays(int mode, int bits, int64_t rows, int64_t N, int cus) {
+    const int64_t work = rows * bits;
+    if (bits > 1280) return true;
+    if (mode == RSR_LABEL)
+        return work * bits >= 5000000000ll || (N >= int64_t{1} << 19 && work >= 480000) ||
+               (N <= int64_t{128} * cus && rows >= 5 * kSparseCountRows);
+    return work >= 2500000 || rows >= 4 * kSparseCountRows || N >= int64_t{1} << 19 ||
+           (N <= int64_t{128} * cus && rows >= 2 * kSparseCountRows);
+}
 
 // Most blocks of a launch of the sparse form (k_sparse.hip), each with an
 // output region of its own.

@@ -265,3 +265,75 @@ def test_counts_against_the_oracle(rsr_ctx, n, K, R_L, R_U, N, bits, mode):
         np.testing.assert_array_equal(match.cpu().numpy()[:, 1], wu)
         if R_U > 20_000:
             assert int(match[:, 1].max()) > 255 * 16 * 4
+
+
+# The same on the rows that the automatic form counts this way at any number of
+# samples.
+@pytest.mark.parametrize("n,K,R_L,R_U,N,bits,mode", [
+    (20, 2, 1, 8192, 1, 2, R.RSR_COUNT),
+    (33, 2, 8193, 63, 129, 3, R.RSR_COUNT),
+    (64, 2, 0, 8300, 2049, 1, R.RSR_COUNT),
+    (295, 2, 300, 8511, 40_001, 6, R.RSR_COUNT),
+    (1250, 2, 100, 2050, 1500, 5, R.RSR_COUNT),
+    (120, 2, 2050, 40, 530_000, 3, R.RSR_COUNT),
+    (40, 3, 4097, 20, 1000, 2, R.RSR_COUNT),
+    (33, 2, 10_257, 63, 5000, 3, R.RSR_LABEL),
+    (340, 3, 300, 10_900, 40_003, 3, R.RSR_LABEL),
+    (300, 2, 2065, 63, 525_000, 3, R.RSR_LABEL),
+])
+def test_counts_of_many_rows(rsr_ctx, n, K, R_L, R_U, N, bits, mode):
+    rng = np.random.default_rng(n + N + bits)
+    lower = np.where(rng.random((R_L, n)) < bits / n, rng.integers(0, K, (R_L, n)), K - 1)
+    upper = np.where(rng.random((R_U, n)) < bits / n, rng.integers(0, K, (R_U, n)), 0)
+    lower[:, 1], upper[:, 0] = K - 2, 1      # no row without a bit
+    lower, upper = lower.astype(np.uint8), upper.astype(np.uint8)
+    model = R.Model(rsr_ctx, np.full((n, K), 1.0 / K))
+    refs = R.Refs(rsr_ctx, n, K, lower, upper)
+    assert mode == R.RSR_COUNT or not refs.consistent
+    xs = R.rsr_sample(rsr_ctx, model, 31, 0, 0, N)
+    if N > 100_000:  # the oracle on the first samples, the other form on all
+        want = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, form=R.RSR_MFMA_FP4,
+                              want_match=mode == R.RSR_COUNT)
+        got = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, want_match=mode == R.RSR_COUNT)
+        for a, b in zip(*((got, want) if mode == R.RSR_COUNT else ((got,), (want,)))):
+            assert torch.equal(a, b)
+    some = min(N, 2000)
+    x = unpack_states(xs[:, :some].cpu().numpy(), n, K)
+    want, wl, wu = oracle.classify(lower, upper, x, mode=1 if mode == R.RSR_COUNT else 0)
+    if mode == R.RSR_COUNT:
+        flags, match = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, want_match=True)
+        np.testing.assert_array_equal(match.cpu().numpy()[:some, 0], wl)
+        np.testing.assert_array_equal(match.cpu().numpy()[:some, 1], wu)
+    else:
+        flags = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode)
+    np.testing.assert_array_equal(flags.cpu().numpy()[:some], want)
+
+
+@pytest.mark.parametrize("n,rows,N,mode", [
+    (40, 2048, 70_000, R.RSR_COUNT), (120, 2100, 200_000, R.RSR_COUNT),
+    (295, 4000, 70_000, R.RSR_COUNT), (295, 4000, 70_000, R.RSR_LABEL),
+    (640, 2048, 70_000, R.RSR_LABEL), (120, 8000, 70_000, R.RSR_LABEL)])
+def test_few_rows_take_the_matrix_cores(rsr_ctx, n, rows, N, mode):
+    """Rows of few bits, too few of them to pay for bit-sliced counters (1.2 to 4
+    times the FP4 form's time): the automatic form takes no longer than FP4."""
+    rng = np.random.default_rng(n)
+    lower = np.where(rng.random((rows, n)) < 0.01, 0, 1).astype(np.uint8)
+    upper = np.where(rng.random((rows, n)) < 0.01, 1, 0).astype(np.uint8)
+    lower[:, 1], upper[:, 0] = 0, 1
+    refs = R.Refs(rsr_ctx, n, 2, lower, upper)
+    assert not refs.consistent
+    model = R.Model(rsr_ctx, np.tile([0.05, 0.95], (n, 1)))
+    xs = R.rsr_sample(rsr_ctx, model, 31, 0, 0, N)
+    us = {}
+    for form in (R.RSR_AUTO, R.RSR_MFMA_FP4):
+        flags = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, form=form)
+        best = float("inf")
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(10):
+                R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, form=form, flags=flags)
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t) * 1e5)
+        us[form] = best
+    assert us[R.RSR_AUTO] < 1.15 * us[R.RSR_MFMA_FP4], us
