@@ -168,6 +168,12 @@ struct Team {
         if (BLOCK) __syncthreads();
         else graph::wave_sync();
     }
+    // At the head of a loop whose body begins with a loop over nodes or edges:
+    // makes the lanes without one wait for the others.  Otherwise the compiler may
+    // send the lanes that skip a like loop before this one straight to the sync
+    // behind it, and on, ahead of the lanes that still write (as with fewer than 64
+    // nodes).
+    __device__ void converge() const { __builtin_amdgcn_wave_barrier(); }
     __device__ bool any(bool b) const {  // also orders the LDS accesses
         if (BLOCK) return __syncthreads_or(b ? 1 : 0) != 0;
         graph::wave_sync();
@@ -289,6 +295,7 @@ __device__ __forceinline__ uint64_t bridgeless(const Team<BLOCK>& tm, const Grou
     set_nodes(tm, g, S, from);
     bool changed = true;
     while (changed) {
+        tm.converge();
         set_nodes(tm, g, T, -1);
         tm.sync();
         changed = false;
@@ -314,6 +321,7 @@ __device__ __forceinline__ uint64_t bridgeless(const Team<BLOCK>& tm, const Grou
     // Ears: T marks the searched nodes outside, by_u and by_v the edges that
     // marked their end u or v.
     while (open) {
+        tm.converge();
         set_nodes(tm, g, T, -1);
         for (int e = tm.lane(); e < g.n_edges; e += tm.size())
             by_u[edge_slot(e)] = by_v[edge_slot(e)] = 0;

@@ -103,3 +103,43 @@ def test_listed_samples(rsr_ctx, N, share, offset):
         np.testing.assert_array_equal(got[offset:offset + N], want, err_msg=kind)
         assert (got[:offset] == 77).all() and (got[offset + N:] == 77).all()
         assert int(n_eval) == int((flags == 0).sum())
+
+
+@pytest.mark.parametrize("n,m,up,N,seed", [
+    (7, 12, 0.85, 5000, 7), (33, 80, 0.9, 20_000, 33), (50, 120, 0.9, 50_000, 50),
+    (63, 150, 0.9, 20_000, 63), (64, 154, 0.9, 20_000, 66), (90, 216, 0.92, 20_000, 90),
+    (150, 460, 0.9, 3000, 151), (200, 470, 0.93, 3000, 205)])
+def test_two_edge_connectivity_of_local_graphs(rsr_ctx, n, m, up, N, seed):
+    """Near neighbours joined, so that many samples have a single bridge or hang
+    together by a few ears; lanes and waves without a node (fewer than 64, or not a
+    multiple of 64) beside those that have one."""
+    rng = np.random.default_rng(seed)
+    pos = rng.random((n, 2))
+    iu, ju = np.triu_indices(n, k=1)
+    d = np.hypot(*(pos[iu] - pos[ju]).T)
+    near = {(int(np.argmin(np.hypot(*(pos[:v] - pos[v]).T))), v) for v in range(1, n)}
+    for v in range(n):  # and two neighbours at least
+        near |= {(min(int(w), v), max(int(w), v))
+                 for w in np.argsort(np.hypot(*(pos - pos[v]).T))[1:3]}
+    for k in np.argsort(d, kind="stable"):
+        if len(near) >= m:
+            break
+        near.add((int(iu[k]), int(ju[k])))
+    ends = np.array(sorted(near, key=lambda e: float(np.hypot(*(pos[e[0]] - pos[e[1]])))), np.int32)
+    g = {"n_nodes": n, "edge_u": ends[:, 0].copy(), "edge_v": ends[:, 1].copy(), "source": 0,
+         "sink": n - 1}
+    system = R.System(rsr_ctx, g, kind="global", level=2)
+    # Two thirds of the edges are sure, so that the rest decide.
+    q = np.where(rng.random(len(ends)) < 0.6, 1.0 - (1.0 - up) / 20, up)
+    model = R.Model(rsr_ctx, np.stack([1.0 - q, q], axis=1))
+    xs = R.rsr_sample(rsr_ctx, model, 7, 0, 0, N)
+    x = unpack_states(xs.cpu().numpy(), len(ends), 2)
+    want, _ = oracle.eval_unknown_global(g, x, None, which=1, level=2)
+    assert 0 < want.sum() < N
+    Y = R.rsr_eval_unknown(rsr_ctx, system, xs, N, None, which=R.RSR_ALL)
+    np.testing.assert_array_equal(Y.cpu().numpy(), want)
+    # The same samples listed, in groups of others.
+    flags = torch.from_numpy((rng.random(N) < 0.4).astype(np.uint8)).to(rsr_ctx.device)
+    Y = R.rsr_eval_unknown(rsr_ctx, system, xs, N, flags).cpu().numpy()
+    open_ = flags.cpu().numpy() == 0
+    np.testing.assert_array_equal(Y[open_], want[open_])
