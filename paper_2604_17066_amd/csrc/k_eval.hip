@@ -37,6 +37,8 @@
 // connectivity of 125784 listed samples on 59 / 262, with the listing, 429 ->
 // 89 us.  The listing took 32 to 67 us with one atomic per wave on a common
 // counter and takes about 6 us for 1e6 flags.
+#include <climits>
+
 #include "bits.h"
 #include "graph_search.h"
 #include "sample_list.h"
@@ -538,29 +540,31 @@ __global__ __launch_bounds__(kWideBlock) void k_global2_wide(
     }
 }
 
-// LDS of a block of `waves` waves.
-size_t connect_lds(int kind, int n_nodes, int n_edges, int waves) {
+// LDS of a block with the tables of `groups` groups.
+size_t connect_lds(int kind, int n_nodes, int n_edges, int groups) {
     return 16 * (static_cast<size_t>(n_edges + 3) >> 2) +
-           8 * static_cast<size_t>(connect_slots(kind, n_nodes, n_edges)) * waves;
+           8 * static_cast<size_t>(connect_slots(kind, n_nodes, n_edges)) * groups;
 }
 
 template <int KIND>
 hipError_t launch_connect(hipStream_t st, const rsr_system* sys, const SegSrc& seg, int plane,
                           int from, int to, const SampleList& list, int which,
                           uint64_t* d_n_evaluated, int cus) {
-    // Four waves a block, fewer where a block would take more than half the LDS.
-    int waves = 4;
-    while (waves > 1 && connect_lds(KIND, sys->n_nodes, sys->n_edges, waves) > kConnectLds / 2)
-        waves >>= 1;
-    const size_t lds = connect_lds(KIND, sys->n_nodes, sys->n_edges, waves);
+    // Where the tables of a block's four waves would take more than half the LDS,
+    // its waves work on one group always.  (With fewer waves a block instead, 20
+    // samples of 4096 edges on 100 nodes took 31 us, 12 now, and 5e4 samples 69,
+    // 27 now; a ladder of 2101 edges 2311 and 4923, 1053 and 2114 now.)
+    constexpr int kWaves = 4;
+    const bool one = connect_lds(KIND, sys->n_nodes, sys->n_edges, kWaves) > kConnectLds / 2;
+    const size_t lds = connect_lds(KIND, sys->n_nodes, sys->n_edges, one ? 1 : kWaves);
     int per_cu = static_cast<int>(kConnectLds / lds);
     if (per_cu > 8) per_cu = 8;
     if (per_cu < 1) per_cu = 1;
     const int64_t need = (seg.total + 63) / 64, cap = static_cast<int64_t>(per_cu) * cus;
     hipLaunchKernelGGL(k_connect<KIND>, dim3(static_cast<unsigned>(need < cap ? need : cap)),
-                       dim3(64 * waves), lds, st, seg, plane_words(sys->n_edges), plane,
+                       dim3(64 * kWaves), lds, st, seg, plane_words(sys->n_edges), plane,
                        sys->d_edges, sys->n_edges, sys->n_nodes, from, to, list, which,
-                       waves > 1 && sys->n_edges >= kBlockEdges ? kBlockGroups * cus : 0,
+                       one ? INT_MAX : sys->n_edges >= kBlockEdges ? kBlockGroups * cus : 0,
                        reinterpret_cast<unsigned long long*>(d_n_evaluated));
     return hipGetLastError();
 }

@@ -143,3 +143,32 @@ def test_two_edge_connectivity_of_local_graphs(rsr_ctx, n, m, up, N, seed):
     Y = R.rsr_eval_unknown(rsr_ctx, system, xs, N, flags).cpu().numpy()
     open_ = flags.cpu().numpy() == 0
     np.testing.assert_array_equal(Y[open_], want[open_])
+
+
+def test_large_tables_keep_a_block_busy(rsr_ctx):
+    """A few samples on a graph whose tables leave a block room for one group: its
+    waves share the sweeps, so four times the edges of a graph with room for four
+    groups take about a quarter more, not three times as long."""
+    rng = np.random.default_rng(5)
+    us = []
+    for m in (1000, 4000):
+        eu = np.concatenate([np.arange(99), rng.integers(0, 100, m - 99)]).astype(np.int32)
+        ev = np.concatenate([np.arange(1, 100), rng.integers(0, 100, m - 99)]).astype(np.int32)
+        g = {"n_nodes": 100, "edge_u": eu, "edge_v": ev, "source": 0, "sink": 99}
+        system = R.System(rsr_ctx, g)
+        model = R.Model(rsr_ctx, np.tile([0.7, 0.3], (m, 1)))
+        xs = R.rsr_sample(rsr_ctx, model, 7, 0, 0, 20)
+        Y = R.rsr_eval_unknown(rsr_ctx, system, xs, 20, None, which=R.RSR_ALL)
+        x = unpack_states(xs.cpu().numpy(), m, 2)
+        np.testing.assert_array_equal(Y.cpu().numpy(), oracle.eval_unknown(g, x, None, which=1)[0])
+        best = float("inf")
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(50):
+                R.rsr_eval_unknown(rsr_ctx, system, xs, 20, None, which=R.RSR_ALL, Y=Y)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 20)
+        us.append(best)
+    assert us[1] < 2 * us[0], us
