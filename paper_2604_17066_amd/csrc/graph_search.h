@@ -79,7 +79,7 @@ struct GlobalSets {
     uint16_t* depth;    // [n_nodes]
 };
 
-__device__ __forceinline__ int global_words(int n_nodes, int n_edges) {
+__host__ __device__ __forceinline__ int global_words(int n_nodes, int n_edges) {
     // reach + covered + parent and depth as 16-bit pairs
     return ((n_nodes + 31) >> 5) + ((n_edges + 31) >> 5) + 2 * ((n_nodes + 1) >> 1);
 }

@@ -26,7 +26,8 @@
 //     (noting every node's marking edge), and a node with an edge into the
 //     class other than its marking edge closes a cycle and joins.  If none
 //     does, the seed is a bridge.  A node with fewer than two usable edges
-//     settles most of the others at the start.
+//     settles most of the others at the start.  Where ears would take many
+//     rounds the samples go to k_walk2, one sample per wave (launch_global2).
 //
 // With few groups of samples a whole block works on one (a sweep is a chain of
 // dependent LDS steps per 64 or 256 edges), else a wave.
@@ -131,6 +132,9 @@ __global__ __launch_bounds__(kLabelBlock) void k_label(SegSrc seg, int64_t chunk
 }
 
 enum Connect { kSt, kGlobal1, kGlobal2 };
+
+// Y of a sample that k_connect<kGlobal2> leaves to k_walk2.
+constexpr uint32_t kOpen = 2;
 
 // u64 words of a wave's edge table: the 32 edges of a packed word and two
 // words of padding, so that the transpose's stores do not all hit one bank.
@@ -271,13 +275,14 @@ __device__ __forceinline__ void grow_all(const Team<BLOCK>& tm, const Group& g, 
     }
 }
 
-// Of the connected samples `open`, those without a bridge.  tree: a spanning
-// tree's edges; S, T: node sets; by_u, by_v: edge tables; seeded: one word.
+// Of the connected samples `open`, those without a bridge; on return `open` holds
+// the ones that `ears` rounds of ears have not settled.  tree: a spanning tree's
+// edges; S, T: node sets; by_u, by_v: edge tables; seeded: one word.
 template <bool BLOCK>
 __device__ __forceinline__ uint64_t bridgeless(const Team<BLOCK>& tm, const Group& g, int from,
-                                               uint64_t open, const uint64_t* tree, uint64_t* S,
-                                               uint64_t* T, uint64_t* by_u, uint64_t* by_v,
-                                               uint64_t* seeded) {
+                                               int ears, uint64_t& open, const uint64_t* tree,
+                                               uint64_t* S, uint64_t* T, uint64_t* by_u,
+                                               uint64_t* by_v, uint64_t* seeded) {
     // Two usable edges at every node?  S counts the first, T the second.
     set_nodes(tm, g, S, -1);
     set_nodes(tm, g, T, -1);
@@ -322,7 +327,7 @@ __device__ __forceinline__ uint64_t bridgeless(const Team<BLOCK>& tm, const Grou
     open &= ~good;
     // Ears: T marks the searched nodes outside, by_u and by_v the edges that
     // marked their end u or v.
-    while (open) {
+    for (int round = 0; open && round < ears; ++round) {
         tm.converge();
         set_nodes(tm, g, T, -1);
         for (int e = tm.lane(); e < g.n_edges; e += tm.size())
@@ -386,8 +391,9 @@ __device__ __forceinline__ uint64_t bridgeless(const Team<BLOCK>& tm, const Grou
 
 template <int KIND, bool BLOCK>
 __device__ __forceinline__ void eval_groups(const SegSrc& seg, int PW, int plane, Group g, int from,
-                                            int to, const SampleList& list, const uint32_t* before,
-                                            int which, int64_t total, Team<BLOCK> tm) {
+                                            int to, int ears, const SampleList& list,
+                                            const uint32_t* before, int which, int64_t total,
+                                            Team<BLOCK> tm) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const int slots = edge_slots(g.n_edges);
@@ -442,7 +448,7 @@ __device__ __forceinline__ void eval_groups(const SegSrc& seg, int PW, int plane
         }
         tm.sync();
 
-        uint64_t up;
+        uint64_t up, open = 0;
         if (KIND == kSt) {
             up = st_connected(tm, g, from, to, S, T);
         } else {
@@ -452,11 +458,15 @@ __device__ __forceinline__ void eval_groups(const SegSrc& seg, int PW, int plane
             tm.sync();
             grow_all<KIND == kGlobal2>(tm, g, S, tree);
             up = all_nodes(tm, g, S);
-            if (KIND == kGlobal2 && up)
-                up = bridgeless(tm, g, to, up, tree, S, T, tree + slots, tree + 2 * slots, T + g.n_nodes);
+            if (KIND == kGlobal2 && up) {
+                open = up;
+                up = bridgeless(tm, g, to, ears, open, tree, S, T, tree + slots, tree + 2 * slots,
+                                T + g.n_nodes);
+            }
         }
         if (valid && (!BLOCK || wave == 0))
-            global_ptr(seg_Y(seg, job))[h] = static_cast<uint8_t>((up >> lane) & 1u);
+            global_ptr(seg_Y(seg, job))[h] =
+                static_cast<uint8_t>((open >> lane) & 1u ? kOpen : (up >> lane) & 1u);
         tm.sync();
     }
 }
@@ -464,8 +474,9 @@ __device__ __forceinline__ void eval_groups(const SegSrc& seg, int PW, int plane
 template <int KIND>
 __global__ __launch_bounds__(256) void k_connect(SegSrc seg, int PW, int plane,
                                                  const uint32_t* __restrict__ edges, int n_edges,
-                                                 int n_nodes, int from, int to, SampleList list,
-                                                 int which, int block_groups,
+                                                 int n_nodes, int from, int to, int ears,
+                                                 SampleList list, int which, int block_groups,
+                                                 int few,
                                                  unsigned long long* __restrict__ n_evaluated) {
     extern __shared__ uint64_t lds64[];
     __shared__ uint32_t before[kListRegions + 1];
@@ -475,6 +486,7 @@ __global__ __launch_bounds__(256) void k_connect(SegSrc seg, int PW, int plane,
     const int64_t total = which == RSR_ALL ? seg.total : list_prefix(list, before);
     if (blockIdx.x == 0 && tid == 0 && n_evaluated)
         *n_evaluated = static_cast<unsigned long long>(total);
+    if (KIND == kGlobal2 && total <= few) return;  // k_walk2 takes them all
     const int64_t groups = (total + 63) >> 6;
     const bool block = groups <= block_groups;
     if (static_cast<int64_t>(blockIdx.x) * (block ? 1 : waves) >= groups) return;  // per block
@@ -484,59 +496,73 @@ __global__ __launch_bounds__(256) void k_connect(SegSrc seg, int PW, int plane,
     __syncthreads();
     uint64_t* x = lds64 + (((n_edges + 3) >> 2) << 1);
     if (block) {
-        eval_groups<KIND>(seg, PW, plane, Group{x, s_edges, n_edges, n_nodes}, from, to, list,
+        eval_groups<KIND>(seg, PW, plane, Group{x, s_edges, n_edges, n_nodes}, from, to, ears, list,
                           before, which, total, Team<true>{red});
     } else {
         x += wave * connect_slots(KIND, n_nodes, n_edges);
-        eval_groups<KIND>(seg, PW, plane, Group{x, s_edges, n_edges, n_nodes}, from, to, list,
+        eval_groups<KIND>(seg, PW, plane, Group{x, s_edges, n_edges, n_nodes}, from, to, ears, list,
                           before, which, total, Team<false>{red});
     }
 }
 
-constexpr int kWideBlock = 256;
-constexpr int kWideWaves = kWideBlock / 64;
+constexpr int kWalkBlock = 256;
+constexpr int kWalkWaves = kWalkBlock / 64;
 
 // Two-edge-connectivity, one sample per wavefront by the tree-cycle walk of
-// graph_search.h: for graphs whose tables of 64 samples exceed the LDS (from
-// about 3400 edges and 2500 nodes on).
-__global__ __launch_bounds__(kWideBlock) void k_global2_wide(
+// graph_search.h: all samples where there are at most `few`, else those that
+// k_connect has left open.  Sample j is wave j's modulo the number of waves, so
+// that neighbours, which are often open together, go to different ones.
+__global__ __launch_bounds__(kWalkBlock) void k_walk2(
     SegSrc seg, const uint32_t* __restrict__ edges, int n_edges, int n_nodes, SampleList list,
-    int which, unsigned long long* __restrict__ n_evaluated) {
+    int which, int64_t few, unsigned long long* __restrict__ n_evaluated) {
     extern __shared__ uint32_t lds[];
-    __shared__ uint32_t before[kListRegions + 1];
+    uint32_t* s_edges = lds;
+    uint32_t* sets = lds + n_edges;
+    uint32_t* before = sets + kWalkWaves * graph::global_words(n_nodes, n_edges);  // for a list
     const int64_t total = which == RSR_ALL ? seg.total : list_prefix(list, before);
     if (blockIdx.x == 0 && threadIdx.x == 0 && n_evaluated)
         *n_evaluated = static_cast<unsigned long long>(total);
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * kWideWaves;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * kWalkWaves;
     if (first >= total) return;  // uniform per block
 
-    uint32_t* s_edges = lds;
-    for (int e = threadIdx.x; e < n_edges; e += kWideBlock) s_edges[e] = edges[e];
+    for (int e = threadIdx.x; e < n_edges; e += kWalkBlock) s_edges[e] = edges[e];
     __syncthreads();
     const graph::GlobalSets g = graph::global_sets(
-        lds + n_edges + wave * graph::global_words(n_nodes, n_edges), n_nodes, n_edges);
+        sets + wave * graph::global_words(n_nodes, n_edges), n_nodes, n_edges);
     const int edge_rounds = (n_edges + 63) >> 6;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kWideWaves;
-    for (int64_t j = first + wave; j < total; j += stride) {
-        const int64_t g_idx =
-            which == RSR_ALL ? j : list_at(list, before, static_cast<uint32_t>(j));
-        int job;
-        int64_t h, xstride;
-        seg_locate(seg, g_idx, job, h);
-        const uint32_t* xs = seg_words(seg, job, xstride);
-        uint64_t usable = 0;  // plane 0 = [x >= 1]
-        for (int k = 0; k < edge_rounds; ++k) {
-            const int e = lane + 64 * k;
-            if (e < n_edges) {
-                const uint32_t word = xs[static_cast<int64_t>(e >> 5) * xstride + h];
-                usable |= static_cast<uint64_t>((word >> (e & 31)) & 1u) << k;
-            }
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kWalkWaves;
+    for (int64_t j0 = first + wave; j0 < total; j0 += 64 * stride) {
+        // Lane l looks at sample j0 + l * stride.
+        const int64_t mine = j0 + lane * stride;
+        bool todo = mine < total;
+        int job = 0;
+        int64_t h = 0;
+        if (todo) {
+            seg_locate(seg, which == RSR_ALL ? mine : list_at(list, before, static_cast<uint32_t>(mine)),
+                       job, h);
+            if (total > few) todo = global_ptr(seg_Y(seg, job))[h] == kOpen;
         }
-        const bool up = graph::two_edge_connected(usable, s_edges, n_edges, n_nodes, g);
-        if (lane == 0) seg_Y(seg, job)[h] = up ? 1 : 0;
-        graph::wave_sync();
+        for (uint64_t left = __ballot(todo); left; left &= left - 1) {
+            const int from = __ffsll(static_cast<unsigned long long>(left)) - 1;
+            const int jb = __builtin_amdgcn_readlane(job, from);
+            const int64_t at = static_cast<uint32_t>(
+                __builtin_amdgcn_readlane(static_cast<int>(h), from));  // below 2^31
+            int64_t xstride;
+            const uint32_t* xs = seg_words(seg, jb, xstride);
+            uint64_t usable = 0;  // plane 0 = [x >= 1]
+            for (int k = 0; k < edge_rounds; ++k) {
+                const int e = lane + 64 * k;
+                if (e < n_edges) {
+                    const uint32_t word = xs[static_cast<int64_t>(e >> 5) * xstride + at];
+                    usable |= static_cast<uint64_t>((word >> (e & 31)) & 1u) << k;
+                }
+            }
+            const bool up = graph::two_edge_connected(usable, s_edges, n_edges, n_nodes, g);
+            if (lane == 0) seg_Y(seg, jb)[at] = up ? 1 : 0;
+            graph::wave_sync();
+        }
     }
 }
 
@@ -549,7 +575,7 @@ size_t connect_lds(int kind, int n_nodes, int n_edges, int groups) {
 template <int KIND>
 hipError_t launch_connect(hipStream_t st, const rsr_system* sys, const SegSrc& seg, int plane,
                           int from, int to, const SampleList& list, int which,
-                          uint64_t* d_n_evaluated, int cus) {
+                          uint64_t* d_n_evaluated, int cus, int ears = 0, int few = 0) {
     // Where the tables of a block's four waves would take more than half the LDS,
     // its waves work on one group always.  (With fewer waves a block instead, 20
     // samples of 4096 edges on 100 nodes took 31 us, 12 now, and 5e4 samples 69,
@@ -563,9 +589,54 @@ hipError_t launch_connect(hipStream_t st, const rsr_system* sys, const SegSrc& s
     const int64_t need = (seg.total + 63) / 64, cap = static_cast<int64_t>(per_cu) * cus;
     hipLaunchKernelGGL(k_connect<KIND>, dim3(static_cast<unsigned>(need < cap ? need : cap)),
                        dim3(64 * kWaves), lds, st, seg, plane_words(sys->n_edges), plane,
-                       sys->d_edges, sys->n_edges, sys->n_nodes, from, to, list, which,
-                       one ? INT_MAX : sys->n_edges >= kBlockEdges ? kBlockGroups * cus : 0,
+                       sys->d_edges, sys->n_edges, sys->n_nodes, from, to, ears, list, which,
+                       one ? INT_MAX : sys->n_edges >= kBlockEdges ? kBlockGroups * cus : 0, few,
                        reinterpret_cast<unsigned long long*>(d_n_evaluated));
+    return hipGetLastError();
+}
+
+// Two-edge-connectivity: k_connect, then k_walk2 for what it leaves.
+//
+// A walk takes a wave the same time whatever the graph is like; k_connect takes 64
+// samples at once but in sweeps, some for every step of the graph's depth and,
+// with ears, for every round of them.  One round settles one ear per sample, so on
+// a ladder or a chain of rings there are as many as links.  Hence:
+//  * Ears only on graphs of three edges a node or more, where nearly every sample
+//    is settled in a round or two (5e4 samples, us without / with four rounds: 59
+//    nodes and 262 edges 41 / 29, 200 / 800 119 / 42; but a 30 x 30 lattice with 1e3
+//    samples 795 / 1069, a ladder of 1402 nodes 5698 / 12298, and 733419 until all
+//    were settled).
+//  * All samples to the walk where its waves take them in one go, but on shallow
+//    graphs of some size (1000 samples, us by walks / k_connect: 50 nodes and 120
+//    edges 14 / 35, 59 / 262 20 / 24, ring of 500 588 / 780, roads of 288 nodes 124
+//    / 163; but 119 / 295 33 / 26, 200 / 800 52 / 34, 500 / 1250 175 / 38).
+//  * All samples to the walk where one group's tables exceed the LDS.
+constexpr int kEars = 4;
+
+hipError_t launch_global2(hipStream_t st, const rsr_system* sys, const SegSrc& seg,
+                          const SampleList& list, int which, uint64_t* d_n_evaluated, int cus) {
+    const size_t lds = sizeof(uint32_t) *
+        (static_cast<size_t>(sys->n_edges) +
+         kWalkWaves * static_cast<size_t>(graph::global_words(sys->n_nodes, sys->n_edges)) +
+         (which == RSR_ALL ? 0 : kListRegions + 1));
+    // The LDS of a CU, taken in pieces of 1280 bytes.
+    int64_t per_cu = static_cast<int64_t>(160 * 1024 / ((lds + 1279) / 1280 * 1280));
+    if (per_cu > 8) per_cu = 8;
+    const int64_t cap = per_cu * cus;
+    const int ears = sys->n_edges >= 3 * sys->n_nodes ? kEars : 0;
+    const bool shallow = sys->n_nodes >= 96 && sys->n_edges >= 2 * sys->n_nodes && sys->depth <= 40;
+    int64_t few = shallow ? 0 : cap * kWalkWaves;
+    if (connect_lds(kGlobal2, sys->n_nodes, sys->n_edges, 1) > kConnectLds) few = INT64_MAX;
+    if (seg.total > few) {
+        const hipError_t e =
+            launch_connect<kGlobal2>(st, sys, seg, 0, sys->tree_from, sys->class_from, list, which,
+                                     nullptr, cus, ears, static_cast<int>(few));
+        if (e != hipSuccess) return e;
+    }
+    const int64_t need = (seg.total + kWalkWaves - 1) / kWalkWaves;
+    hipLaunchKernelGGL(k_walk2, dim3(static_cast<unsigned>(need < cap ? need : cap)),
+                       dim3(kWalkBlock), lds, st, seg, sys->d_edges, sys->n_edges, sys->n_nodes,
+                       list, which, few, reinterpret_cast<unsigned long long*>(d_n_evaluated));
     return hipGetLastError();
 }
 
@@ -588,21 +659,7 @@ hipError_t launch_eval(hipStream_t st, const rsr_system* sys, const SegSrc& seg,
         if (sys->level < 2)
             return launch_connect<kGlobal1>(st, sys, seg, 0, sys->class_from, 0, list, which,
                                             d_n_evaluated, cus);
-        if (connect_lds(kGlobal2, sys->n_nodes, sys->n_edges, 1) > kConnectLds) {
-            const int64_t need = (seg.total + kWideWaves - 1) / kWideWaves, cap = cus * 8;
-            const size_t lds = sizeof(uint32_t) *
-                (static_cast<size_t>(sys->n_edges) +
-                 kWideWaves * static_cast<size_t>(((sys->n_nodes + 31) >> 5) +
-                                                  ((sys->n_edges + 31) >> 5) +
-                                                  2 * ((sys->n_nodes + 1) >> 1)));
-            hipLaunchKernelGGL(k_global2_wide, dim3(static_cast<unsigned>(need < cap ? need : cap)),
-                               dim3(kWideBlock), lds, st, seg, sys->d_edges, sys->n_edges,
-                               sys->n_nodes, list, which,
-                               reinterpret_cast<unsigned long long*>(d_n_evaluated));
-            return hipGetLastError();
-        }
-        return launch_connect<kGlobal2>(st, sys, seg, 0, sys->tree_from, sys->class_from, list,
-                                        which, d_n_evaluated, cus);
+        return launch_global2(st, sys, seg, list, which, d_n_evaluated, cus);
     }
     return launch_connect<kSt>(st, sys, seg, sys->level - 1, sys->source, sys->sink, list, which,
                                d_n_evaluated, cus);

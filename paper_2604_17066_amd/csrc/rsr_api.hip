@@ -819,6 +819,17 @@ rsr_status rsr_system_create(rsr_ctx* ctx, const rsr_system_desc* d, rsr_system*
     }
     s->tree_from = static_cast<int>(std::min_element(degree.begin(), degree.end()) - degree.begin());
     s->class_from = static_cast<int>(std::max_element(degree.begin(), degree.end()) - degree.begin());
+    if (global && d->level == 2) {
+        std::vector<uint8_t> near(d->n_nodes, 0);
+        near[s->tree_from] = 1;
+        for (std::vector<uint8_t> next = near;; ++s->depth, near = next) {
+            for (uint32_t uv : packed) {
+                next[uv >> 16] |= near[uv & 0xFFFFu];
+                next[uv & 0xFFFFu] |= near[uv >> 16];
+            }
+            if (next == near) break;
+        }
+    }
     hipError_t e = rsr::dev_malloc(&s->d_edges, sizeof(uint32_t) * packed.size());
     if (e == hipSuccess)
         e = hipMemcpy(s->d_edges, packed.data(), sizeof(uint32_t) * packed.size(),

@@ -174,6 +174,7 @@ struct rsr_system {
     // two-edge-connected nodes start (k_eval.hip).  All edges of the first may
     // be tree edges, so it is a node of least degree, the other of the most.
     int tree_from = 0, class_from = 0;
+    int depth = 0;  // steps from tree_from to the farthest node (level 2)
     // RSR_SYS_HOST_CALLBACK: the system state of a state vector, on the host.
     int32_t (*phi)(const uint8_t* x, int32_t n, void* user) = nullptr;
     void* user = nullptr;

@@ -172,3 +172,134 @@ def test_large_tables_keep_a_block_busy(rsr_ctx):
             best = min(best, a.elapsed_time(b) * 20)
         us.append(best)
     assert us[1] < 2 * us[0], us
+
+
+def _cliques(count, size):
+    """A chain of cliques, two links between neighbours: an ear for every link."""
+    e = []
+    for k in range(count):
+        e += [(size * k + a, size * k + b) for a in range(size) for b in range(a + 1, size)]
+        if k:
+            e += [(size * (k - 1), size * k), (size * (k - 1) + 1, size * k + 1)]
+    return size * count, e
+
+
+def _roads(side, pieces):
+    """A lattice of crossings whose roads are chains of `pieces` edges."""
+    n, e = side * side, []
+    for a, b in ([(r * side + c, r * side + c + 1) for r in range(side) for c in range(side - 1)] +
+                 [(r * side + c, r * side + c + side) for r in range(side - 1) for c in range(side)]):
+        for _ in range(pieces - 1):
+            e.append((a, n))
+            a, n = n, n + 1
+        e.append((a, b))
+    return n, e
+
+
+def _ladder(m):
+    return 2 * m, ([(i, i + 1) for i in range(m - 1)] + [(m + i, m + i + 1) for i in range(m - 1)] +
+                   [(i, m + i) for i in range(m)])
+
+
+def _dense(n, m, rng):
+    return n, [(i, i + 1) for i in range(n - 1)] + rng.integers(0, n, (m - n + 1, 2)).tolist()
+
+
+# More samples than the walk's waves take at once (8192), so that the search of 64
+# goes first, with ears or without, and leaves some; few samples on a shallow
+# graph, which it takes too, and on others, which go to the walk; tables just
+# within the LDS and beyond it.
+@pytest.mark.parametrize("name,up,N", [
+    ("ladder", 0.99, 9001), ("roads", 0.996, 8300), ("cliques", 0.97, 8193),
+    ("short cliques", 0.9, 20_000), ("shallow", 0.85, 700), ("deep", 0.999, 300),
+    ("tables fit", 0.2, 130), ("tables too large", 0.2, 130)])
+def test_two_edge_connectivity_by_search_and_walk(rsr_ctx, name, up, N):
+    rng = np.random.default_rng(len(name))
+    n, e = {"ladder": lambda: _ladder(60), "roads": lambda: _roads(7, 3),
+            "cliques": lambda: _cliques(40, 8), "short cliques": lambda: _cliques(5, 8),
+            "shallow": lambda: _dense(120, 300, rng), "deep": lambda: _ladder(130),
+            "tables fit": lambda: _dense(200, 4000, rng),
+            "tables too large": lambda: _dense(200, 4096, rng)}[name]()
+    ends = np.array(e, np.int32)
+    g = {"n_nodes": n, "edge_u": ends[:, 0].copy(), "edge_v": ends[:, 1].copy(), "source": 0,
+         "sink": n - 1}
+    system = R.System(rsr_ctx, g, kind="global", level=2)
+    if name == "shallow":  # the first edges are the only path to the ends
+        up = np.where(np.bincount(ends.ravel(), minlength=n)[ends].min(axis=1) < 4, 0.995, up)
+    q = np.broadcast_to(up, len(e)).astype(np.float64)
+    model = R.Model(rsr_ctx, np.stack([1.0 - q, q], axis=1))
+    xs = R.rsr_sample(rsr_ctx, model, 7, 0, 0, N)
+    # The oracle on the first samples; the others in parts of 4000, which the walk
+    # takes alone (but on shallow graphs).
+    some = min(N, 130 if len(e) < 1000 else 16)
+    x = unpack_states(xs[:, :some].cpu().numpy(), len(e), 2)
+    first, _ = oracle.eval_unknown_global(g, x, None, which=1, level=2)
+    want = np.concatenate([
+        R.rsr_eval_unknown(rsr_ctx, system, R.rsr_sample(rsr_ctx, model, 7, 0, at, part), part, None,
+                           which=R.RSR_ALL).cpu().numpy()
+        for at in range(0, N, 4000) for part in [min(4000, N - at)]])
+    np.testing.assert_array_equal(want[:some], first)
+    n_eval = torch.zeros(1, dtype=torch.int64, device=rsr_ctx.device)
+    Y = R.rsr_eval_unknown(rsr_ctx, system, xs, N, None, which=R.RSR_ALL, n_evaluated=n_eval)
+    np.testing.assert_array_equal(Y.cpu().numpy(), want)
+    assert int(n_eval) == N
+    assert name == "shallow" or 0 < want.sum() < N
+    flags = torch.from_numpy((rng.random(N) < 0.05).astype(np.uint8)).to(rsr_ctx.device)
+    open_ = flags.cpu().numpy() == 0
+    Y = R.rsr_eval_unknown(rsr_ctx, system, xs, N, flags, n_evaluated=n_eval)
+    np.testing.assert_array_equal(Y.cpu().numpy(), np.where(open_, want, 0))
+    assert int(n_eval) == open_.sum()
+
+
+def test_two_edge_connectivity_in_a_plan(rsr_ctx):
+    """Jobs of different sizes share the search and the walk."""
+    n, e = _roads(5, 2)
+    ends = np.array(e, np.int32)
+    g = {"n_nodes": n, "edge_u": ends[:, 0].copy(), "edge_v": ends[:, 1].copy(), "source": 0,
+         "sink": n - 1}
+    m = len(e)
+    system = R.System(rsr_ctx, g, kind="global", level=2)
+    lower = np.ones((m, m), np.uint8) - np.eye(m, dtype=np.uint8)
+    refs = R.Refs(rsr_ctx, m, 2, lower[:9], np.ones((1, m), np.uint8))
+    model = R.Model(rsr_ctx, np.tile([0.02, 0.98], (m, 1)))
+    jobs = [{"model": model, "refs": refs, "system": system, "seed": 70 + k, "N": N,
+             "buffers": R.Buffers(rsr_ctx, m, 2, N)} for k, N in enumerate((5000, 77, 3201))]
+    plan = R.Plan(rsr_ctx, jobs, tune=False)
+    plan.run()
+    plan.results()
+    want = []
+    for job in jobs:
+        x = unpack_states(job["buffers"].samples.cpu().numpy(), m, 2)
+        want.append(oracle.eval_unknown_global(g, x, None, which=1, level=2)[0])
+        np.testing.assert_array_equal(job["buffers"].Y.cpu().numpy(), want[-1])
+        job["buffers"].Y.fill_(9)
+    plan.run()
+    plan.results()
+    for job, Y in zip(jobs, want):
+        np.testing.assert_array_equal(job["buffers"].Y.cpu().numpy(), Y)
+    plan.close()
+
+
+def test_many_ears_do_not_take_forever(rsr_ctx):
+    """A ladder has an ear per rung: two-edge-connectivity takes a few times as long
+    as connectivity, not as many times as there are rungs."""
+    n, e = _ladder(500)
+    ends = np.array(e, np.int32)
+    g = {"n_nodes": n, "edge_u": ends[:, 0].copy(), "edge_v": ends[:, 1].copy(), "source": 0,
+         "sink": n - 1}
+    model = R.Model(rsr_ctx, np.tile([0.01, 0.99], (len(e), 1)))
+    ms = []
+    for level in (1, 2):
+        system = R.System(rsr_ctx, g, kind="global", level=level)
+        xs = R.rsr_sample(rsr_ctx, model, 7, 0, 0, 300)
+        Y = R.rsr_eval_unknown(rsr_ctx, system, xs, 300, None, which=R.RSR_ALL)
+        best = float("inf")
+        for _ in range(3):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            R.rsr_eval_unknown(rsr_ctx, system, xs, 300, None, which=R.RSR_ALL, Y=Y)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        ms.append(best)
+    assert ms[1] < 15 * ms[0], ms
