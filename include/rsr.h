@@ -402,7 +402,9 @@ typedef struct {
  *   a file path:      a JSON object whose keys name a device and a segment
  *                     shape (device name, CU count, packed words W, R_L, R_U,
  *                     consistency, matrix-core operands, jobs and samples per
- *                     job) and whose values are the chosen configuration:
+ *                     job, n, K, and whether and how sparse the rows are; an
+ *                     entry without the last four, as written before the sparse
+ *                     form, is kept and not used) and whose values are the chosen configuration:
  *                     {"choice": 0 cascade, 1 popcount per job, 2 int8
  *                     per job, 3 FP4 per job, 4 persistent cascade, 5 sparse;
  *                     "first", "growth", "split": the cascade's round

@@ -643,6 +643,7 @@ static rsr_status build_refs(rsr_ctx* ctx, int32_t n, int32_t K, std::vector<uin
     refs->WR = WR;
     refs->R_L = R_L;
     refs->R_U = R_U;
+    refs->chunks = static_cast<int64_t>(lo_off.back()) + up_off.back();
     // One allocation and one copy for all arrays, 256-byte aligned.
     struct Part {
         void** dst;

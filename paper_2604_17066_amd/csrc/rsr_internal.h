@@ -159,6 +159,7 @@ struct rsr_refs {
     // the rows are too dense (sparse_density).
     bool sparse = false;
     bool sparse_count = false;            // for counting too (kSparseCount...)
+    int64_t chunks = 0;                   // of both sides, whether sparse or not
     uint32_t* d_lower_off = nullptr;      // [ceil(R_L/64) + 1]
     uint16_t* d_lower_idx = nullptr;      // columns of NOT t(r)
     uint32_t* d_upper_off = nullptr;      // [ceil(R_U/64) + 1]

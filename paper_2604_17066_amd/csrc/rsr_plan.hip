@@ -308,14 +308,17 @@ hipError_t enqueue_rest(const rsr_plan* p, int si, hipStream_t st) {
 }
 
 // Tuning-cache key of a segment: the device and every property of the
-// segment that the timing depends on.
+// segment that the timing depends on; the sparse form's on the components and
+// the bits that the rows have set (in chunks of a slice).
 std::string segment_key(const rsr_ctx* ctx, const Segment& s) {
-    char buf[256];
-    std::snprintf(buf, sizeof buf, "%s/cu%d/W%d/RL%lld/RU%lld/c%d/f%d/J%zu/T%lld/M%lld",
+    char buf[320];
+    std::snprintf(buf, sizeof buf,
+                  "%s/cu%d/W%d/RL%lld/RU%lld/c%d/f%d/J%zu/T%lld/M%lld/n%d/K%d/s%d/B%lld",
                   ctx->arch.c_str(), ctx->cu_count, s.W, static_cast<long long>(s.refs->R_L),
                   static_cast<long long>(s.refs->R_U), s.refs->consistent ? 1 : 0,
                   s.refs->KS4 > 0 ? 1 : 0, s.jobs.size(), static_cast<long long>(s.total),
-                  static_cast<long long>(s.max_N));
+                  static_cast<long long>(s.max_N), s.n, s.K, s.refs->sparse ? 1 : 0,
+                  static_cast<long long>(s.refs->chunks));
     return buf;
 }
 

@@ -282,3 +282,37 @@ def test_plan_persistent_timeout_is_reported(rsr_ctx, tmp_path):
         np.testing.assert_array_equal(_np(jb["buffers"].flags), _np(pb.flags), err_msg=f"job {k}")
         assert est[k]["P"] == pe["P"], k
     plan.close()
+
+
+def test_plan_cache_tells_sparse_rows_from_dense_ones(rsr_ctx, tmp_path):
+    """Two sets of rows alike in all sizes, one with few and one with most components
+    constrained: each has its own entry, and an entry of the former key (the first
+    ten fields) is not taken for either."""
+    import json
+    path = tmp_path / "tune.json"
+    cfg = WL.configs.tiny(N=10)
+    n = cfg["n"]
+    rng = np.random.default_rng(4)
+    system = R.System(rsr_ctx, cfg["graph"])
+    model = R.Model(rsr_ctx, cfg["p"])
+
+    def plan(share):
+        lower = np.where(rng.random((50, n)) < share, 0, 1).astype(np.uint8)
+        upper = np.where(rng.random((50, n)) < share, 1, 0).astype(np.uint8)
+        lower[:, 0], upper[:, 0] = 0, 1
+        refs = R.Refs(rsr_ctx, n, 2, lower, upper)
+        assert refs.consistent
+        job = {"model": model, "refs": refs, "system": system, "seed": 3, "N": 4000,
+               "buffers": R.Buffers(rsr_ctx, n, 2, 4000)}
+        R.Plan(rsr_ctx, [job], tune=str(path)).close()
+        return json.loads(path.read_text())
+
+    dense = plan(0.95)
+    assert len(dense) == 1 and all(e["choice"] != 5 for e in dense.values())
+    both = plan(0.05)
+    assert len(both) == 2 and set(dense) < set(both)
+    former = {key.split("/n")[0]: dict(e, choice=0, first=16, growth=4, split=64, tail=0, chunks=0)
+              for key, e in both.items()}
+    path.write_text(json.dumps(former))
+    again = plan(0.05)
+    assert set(former) < set(again) and len(again) == len(former) + 1
