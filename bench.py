@@ -42,6 +42,11 @@ COUNT_TRAFFIC_BYTES = {
 }
 
 
+# "choice" of a tuning cache (rsr_plan_create).
+PLAN_CHOICES = {0: "cascade", 1: "popcount per job", 2: "int8 per job", 3: "fp4 per job",
+                4: "persistent cascade", 5: "sparse"}
+
+
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
@@ -691,9 +696,7 @@ def batched_leg(ctx, ref_scale, reps, Ns=(1 << 18, 1_000_000), cpu_seconds=None)
         # cache's entries in the order of the graphs' reference rows.
         with open(cache) as f:
             entries = json.load(f)
-        names = {0: "cascade", 1: "popcount per job", 2: "int8 per job", 3: "fp4 per job",
-                 4: "persistent cascade"}
-        choices = sorted(({"key": k.split("/", 2)[2], "choice": names.get(v["choice"], "?"),
+        choices = sorted(({"key": k.split("/", 2)[2], "choice": PLAN_CHOICES[v["choice"]],
                            "tail": v["tail"], "first": v["first"], "growth": v["growth"],
                            "split": v["split"], "chunks": v.get("chunks", 0),
                            "classify_ms": v["ms"]} for k, v in entries.items()),

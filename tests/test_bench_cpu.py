@@ -40,3 +40,16 @@ def test_cpu_baseline_budget_fit():
     assert n == 100 and t < 1.0
     n, t, res = bench._fit_to_budget(run, 4.0, 5000, 10**9)  # the first run is enough
     assert n == 5000 and len([c for c in calls if c == 5000]) == 1
+
+
+def test_every_plan_choice_has_a_name():
+    """The classification forms that a plan's tuner can choose, as the library
+    declares them, are the ones that the benchmark names."""
+    import re
+    sys.path.insert(0, ROOT)
+    import bench
+    with open(os.path.join(ROOT, "paper_2604_17066_amd", "csrc", "rsr_plan.hip")) as f:
+        enum = re.search(r"enum Choice \{(.*?)\};", f.read(), re.S).group(1)
+    numbers = {int(v) for v in re.findall(r"=\s*(\d+)", enum)}
+    assert numbers == set(bench.PLAN_CHOICES) and len(numbers) >= 6
+    assert len(set(bench.PLAN_CHOICES.values())) == len(numbers)
