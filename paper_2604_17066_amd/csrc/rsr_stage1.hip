@@ -166,7 +166,9 @@ rsr_status run_stage1(rsr_ctx* ctx, const rsr_model* model, const rsr_system* sy
     const bool consistent = R_L0 == 0 && R_U0 == 0 && sys->kind != RSR_SYS_HOST_CALLBACK;
 
     CurrentDevice guard(ctx->device);
-    const int64_t N = P.N, B = P.picks;
+    // No more than N samples can be picked, so room for N picks will do (and the
+    // sizes below cannot overflow).
+    const int64_t N = P.N, B = std::min<int64_t>(P.picks, N);
     // One block: samples, flags, picks, then an iteration's rows and, right
     // behind them, its sides.
     const auto aligned = [](size_t bytes) { return (bytes + 255) / 256 * 256; };

@@ -50,3 +50,19 @@ def test_many_duplicates(rsr_ctx):
     assert info["duplicates"] > 1_000
     np.testing.assert_array_equal(lo, wlo)
     np.testing.assert_array_equal(up, wup)
+
+
+@pytest.mark.parametrize("picks", [2 ** 40, 2 ** 61, 2 ** 63 - 1])
+def test_more_picks_than_samples(rsr_ctx, picks):
+    """Room for the picks that a sample set can have, not for those asked for: seven
+    components and 2^61 picks would come to a multiple of 2^64 bytes."""
+    graph = {"n_nodes": 5, "edge_u": np.array([0, 0, 1, 1, 2, 3, 0]),
+             "edge_v": np.array([1, 2, 2, 3, 4, 4, 3]), "source": 0, "sink": 4}
+    p = np.tile([0.3, 0.7], (7, 1))
+    model, system = R.Model(rsr_ctx, p), R.System(rsr_ctx, graph)
+    lo, up, info = R.stage1(rsr_ctx, model, system, 500, picks, 1e-9, 1000, 5, 4)
+    wlo, wup, winfo = oracle.stage1(graph, p, 500, 500, 1e-9, 1000, 5, 4)
+    for key in KEYS:
+        assert info[key] == winfo[key], key
+    np.testing.assert_array_equal(lo, wlo)
+    np.testing.assert_array_equal(up, wup)
