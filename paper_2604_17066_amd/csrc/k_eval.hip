@@ -36,7 +36,7 @@
 // Measured against one sample per wave with a bit per node and edge: plain
 // Monte Carlo of 1e6 samples on 119 nodes / 295 edges 1188 -> 68 us; two-edge-
 // connectivity of 125784 listed samples on 59 / 262, with the listing, 429 ->
-// 89 us.  The listing took 32 to 67 us with one atomic per wave on a common
+// 84 us.  The listing took 32 to 67 us with one atomic per wave on a common
 // counter and takes about 6 us for 1e6 flags.
 #include <climits>
 
@@ -602,16 +602,17 @@ hipError_t launch_connect(hipStream_t st, const rsr_system* sys, const SegSrc& s
 // with ears, for every round of them.  One round settles one ear per sample, so on
 // a ladder or a chain of rings there are as many as links.  Hence:
 //  * Ears only on graphs of three edges a node or more, where nearly every sample
-//    is settled in a round or two (5e4 samples, us without / with four rounds: 59
+//    is settled in a few rounds (5e4 samples, us without / with four rounds: 59
 //    nodes and 262 edges 41 / 29, 200 / 800 119 / 42; but a 30 x 30 lattice with 1e3
 //    samples 795 / 1069, a ladder of 1402 nodes 5698 / 12298, and 733419 until all
-//    were settled).
+//    were settled).  59 / 262, 125784 listed samples, with the listing: 129 us with
+//    two rounds, 99 with four, 84 with eight or more.
 //  * All samples to the walk where its waves take them in one go, but on shallow
 //    graphs of some size (1000 samples, us by walks / k_connect: 50 nodes and 120
 //    edges 14 / 35, 59 / 262 20 / 24, ring of 500 588 / 780, roads of 288 nodes 124
 //    / 163; but 119 / 295 33 / 26, 200 / 800 52 / 34, 500 / 1250 175 / 38).
 //  * All samples to the walk where one group's tables exceed the LDS.
-constexpr int kEars = 4;
+constexpr int kEars = 8;
 
 hipError_t launch_global2(hipStream_t st, const rsr_system* sys, const SegSrc& seg,
                           const SampleList& list, int which, uint64_t* d_n_evaluated, int cus) {
