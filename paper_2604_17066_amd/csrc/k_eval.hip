@@ -625,7 +625,7 @@ hipError_t launch_global2(hipStream_t st, const rsr_system* sys, const SegSrc& s
     if (per_cu > 8) per_cu = 8;
     const int64_t cap = per_cu * cus;
     const int ears = sys->n_edges >= 3 * sys->n_nodes ? kEars : 0;
-    const bool shallow = sys->n_nodes >= 96 && sys->n_edges >= 2 * sys->n_nodes && sys->depth <= 40;
+    const bool shallow = sys->n_nodes >= 96 && sys->n_edges >= 2 * sys->n_nodes && sys->shallow;
     int64_t few = shallow ? 0 : cap * kWalkWaves;
     if (connect_lds(kGlobal2, sys->n_nodes, sys->n_edges, 1) > kConnectLds) few = INT64_MAX;
     if (seg.total > few) {

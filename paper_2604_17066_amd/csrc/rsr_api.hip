@@ -823,12 +823,13 @@ rsr_status rsr_system_create(rsr_ctx* ctx, const rsr_system_desc* d, rsr_system*
     if (global && d->level == 2) {
         std::vector<uint8_t> near(d->n_nodes, 0);
         near[s->tree_from] = 1;
-        for (std::vector<uint8_t> next = near;; ++s->depth, near = next) {
+        std::vector<uint8_t> next = near;
+        for (int step = 0; step <= rsr_system::kShallow && !s->shallow; ++step, near = next) {
             for (uint32_t uv : packed) {
                 next[uv >> 16] |= near[uv & 0xFFFFu];
                 next[uv & 0xFFFFu] |= near[uv >> 16];
             }
-            if (next == near) break;
+            s->shallow = next == near;
         }
     }
     hipError_t e = rsr::dev_malloc(&s->d_edges, sizeof(uint32_t) * packed.size());

@@ -167,6 +167,7 @@ struct rsr_refs {
 };
 
 struct rsr_system {
+    static constexpr int kShallow = 40;
     rsr_ctx* ctx = nullptr;
     int kind = RSR_SYS_ST_CONNECTIVITY;
     int n_nodes = 0, n_edges = 0, K = 0, level = 0, source = 0, sink = 0;
@@ -175,7 +176,8 @@ struct rsr_system {
     // two-edge-connected nodes start (k_eval.hip).  All edges of the first may
     // be tree edges, so it is a node of least degree, the other of the most.
     int tree_from = 0, class_from = 0;
-    int depth = 0;  // steps from tree_from to the farthest node (level 2)
+    // Whether every node is within kShallow steps of tree_from (level 2).
+    bool shallow = false;
     // RSR_SYS_HOST_CALLBACK: the system state of a state vector, on the host.
     int32_t (*phi)(const uint8_t* x, int32_t n, void* user) = nullptr;
     void* user = nullptr;
