@@ -229,8 +229,8 @@ rsr_status rsr_sample(rsr_ctx* ctx, const rsr_model* model, uint64_t seed, uint3
  * operands 0 / +-1 and fp32 accumulation, exact because every partial sum
  * is a small integer), RSR_AUTO (for LABEL mode on consistent rows the
  * sparse form, which tests only the components that a row constrains, or the
- * cascade where the rows constrain many of them; else the sparse form for
- * many rows, the FP4 form up to 1280 bits, or the popcount form),
+ * cascade where the rows constrain many of them or are few; else the sparse
+ * form for many rows, the FP4 form up to 1280 bits, or the popcount form),
  * RSR_PERSIST (the cascade with its rounds after round 0 in one persistent,
  * cooperative launch; its grid barriers wait with a time limit, and a
  * barrier that timed out is reported as RSR_EHIP by the next rsr_estimate).
@@ -397,7 +397,8 @@ typedef struct {
  * at least 2^22 samples, or all of them when it has fewer), with results
  * kept in a tuning cache:
  *   tune_cache NULL:  no timing; every segment takes the default
- *                     configuration (the automatic classification form);
+ *                     configuration (the automatic classification form, or the
+ *                     popcount form on rows that are not consistent);
  *   tune_cache "":    every segment is timed, nothing is stored;
  *   a file path:      a JSON object whose keys name a device and a segment
  *                     shape (device name, CU count, packed words W, R_L, R_U,

@@ -885,7 +885,7 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
                     "the persistent cascade takes LABEL mode on consistent rows, N <= 2^31-1");
     uint32_t* match = mode == RSR_COUNT ? d_match : nullptr;
     // RSR_AUTO: for LABEL on consistent rows (each sample stops at its first
-    // match) the sparse form, or the cascade for dense rows; otherwise the
+    // match) the sparse form, or the cascade for dense or few rows; otherwise the
     // sparse count for many sparse rows, else the FP4 matrix-core form, which
     // makes the most tests per second in both modes; popcount beyond 1280 bits.
     if (form == RSR_AUTO && refs->sparse_count && (mode == RSR_COUNT || !refs->consistent) &&
@@ -916,7 +916,8 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
         cb.match[1] = reinterpret_cast<uint32_t*>(ctx->ws.casc_index + 3 * stride);
         cb.stride = stride;
         cb.set_counters(ctx->ws.casc_counters);
-        if (form == RSR_AUTO && refs->sparse) {
+        if (form == RSR_AUTO && refs->sparse &&
+            rsr::sparse_label_pays(refs->n * (refs->K - 1), n_max, N)) {
             RSR_HIP(ctx, rsr::launch_dom_sparse(ctx->stream, refs,
                                                 rsr::single_src(d_samples, N, d_flags, nullptr),
                                                 rsr::JobTiles(), cb, ctx->cu_count));

@@ -291,6 +291,16 @@ __device__ __forceinline__ uint8_t* seg_Y(const SegSrc& s, int j) {
 constexpr int kSparseSmallBits = 384;
 inline double sparse_density(int bits, int64_t rows);
 
+// Whether it is on such rows, the longer side `rows`: with few of them the
+// transposes of many samples take longer than the cascade's one round of plain
+// tests.  1e6 samples, paths and cuts of networks, sparse / cascade in us: 20 bits
+// and up to 16 rows 11 / 8.5; 120 bits 4 rows 11.5 / 8.9, 8 rows 12.2 / 9.3, 16
+// rows 12.3 / 11.9, 20 rows 12.3 / 27.8; 590 bits 4 rows 27 / 22, 16 rows 28 / 33.
+// 1e4 samples: 7.5 / 9.4 with 20 bits, 8 / 12 with 16 rows of 295.
+inline bool sparse_label_pays(int bits, int64_t rows, int64_t N) {
+    return N < int64_t{1} << 17 || rows > (bits <= 64 ? 16 : 8);
+}
+
 // The same for counting every match, where a sample does not stop at its first
 // one: the share of set bits (295 bits, 3e5 samples, 8.8e4 rows 2154 / 3581 us
 // (FP4) at 0.15 and 4262 / 3637 at 0.25; 1250 bits, 1e5 samples, 4.4e4 rows

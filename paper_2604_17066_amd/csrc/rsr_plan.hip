@@ -531,8 +531,9 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
             s.n = jb.refs->n;
             s.K = jb.refs->K;
             s.W = jb.refs->W;
-            s.choice = !jb.refs->consistent ? kBitsPerJob : jb.refs->sparse ? kSparse : kCascade;
-            // Untuned, a segment takes rsr_classify's automatic form, and a
+            s.choice = jb.refs->consistent ? kCascade : kBitsPerJob;
+            // Untuned, a segment of consistent rows takes rsr_classify's automatic
+            // form (the sparse one is set below, when all jobs are known), and a
             // cascade its shape: matrix-core rounds when the reference handle
             // has FP4 operands, growing faster from kWideRows rows per side on.
             const int64_t rows = std::max(jb.refs->R_L, jb.refs->R_U);
@@ -556,6 +557,9 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
     std::vector<int64_t>& host_offsets = p->offsets;
     int64_t max_total = 0, max_words = 0, max_grad = 0;
     for (Segment& s : p->segs) {
+        if (s.refs->consistent && s.refs->sparse &&
+            rsr::sparse_label_pays(s.n * (s.K - 1), std::max(s.refs->R_L, s.refs->R_U), s.total))
+            s.choice = kSparse;
         if (s.total > 0x7FFFFFFFll) {
             free_plan(p);
             return pfail(ctx, RSR_EUNSUPPORTED, "a segment holds more than 2^31-1 samples");

@@ -309,6 +309,22 @@ def test_counts_of_many_rows(rsr_ctx, n, K, R_L, R_U, N, bits, mode):
     np.testing.assert_array_equal(flags.cpu().numpy()[:some], want)
 
 
+def _times(ctx, refs, xs, N, mode, forms):
+    us = {}
+    for form in forms:
+        flags = R.rsr_classify(ctx, refs, xs, N, mode=mode, form=form)
+        best = float("inf")
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for _ in range(20):
+                R.rsr_classify(ctx, refs, xs, N, mode=mode, form=form, flags=flags)
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t) * 5e4)
+        us[form] = best
+    return us
+
+
 @pytest.mark.parametrize("n,rows,N,mode", [
     (40, 2048, 70_000, R.RSR_COUNT), (120, 2100, 200_000, R.RSR_COUNT),
     (295, 4000, 70_000, R.RSR_COUNT), (295, 4000, 70_000, R.RSR_LABEL),
@@ -324,16 +340,18 @@ def test_few_rows_take_the_matrix_cores(rsr_ctx, n, rows, N, mode):
     assert not refs.consistent
     model = R.Model(rsr_ctx, np.tile([0.05, 0.95], (n, 1)))
     xs = R.rsr_sample(rsr_ctx, model, 31, 0, 0, N)
-    us = {}
-    for form in (R.RSR_AUTO, R.RSR_MFMA_FP4):
-        flags = R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, form=form)
-        best = float("inf")
-        for _ in range(5):
-            torch.cuda.synchronize()
-            t = time.perf_counter()
-            for _ in range(10):
-                R.rsr_classify(rsr_ctx, refs, xs, N, mode=mode, form=form, flags=flags)
-            torch.cuda.synchronize()
-            best = min(best, (time.perf_counter() - t) * 1e5)
-        us[form] = best
+    us = _times(rsr_ctx, refs, xs, N, mode, (R.RSR_AUTO, R.RSR_MFMA_FP4))
     assert us[R.RSR_AUTO] < 1.15 * us[R.RSR_MFMA_FP4], us
+
+
+@pytest.mark.parametrize("n,rows", [(20, 5), (20, 16), (120, 6), (1250, 3)])
+def test_few_rows_and_many_samples_take_the_cascade(rsr_ctx, n, rows):
+    """A handful of rows on 1e6 samples: no slower than one round of plain tests."""
+    rng = np.random.default_rng(n)
+    lower, upper = _rows(rng, rows, rows, n, 2, 4)
+    refs = R.Refs(rsr_ctx, n, 2, lower, upper)
+    assert refs.consistent
+    N = 1_000_000
+    xs = R.rsr_sample(rsr_ctx, R.Model(rsr_ctx, _model(n, 2, 4)), 31, 0, 0, N)
+    us = _times(rsr_ctx, refs, xs, N, R.RSR_LABEL, (R.RSR_AUTO, R.RSR_POPCOUNT))
+    assert us[R.RSR_AUTO] < 1.12 * us[R.RSR_POPCOUNT], us
