@@ -84,10 +84,10 @@ struct SparseList {
     int64_t stride;
 };
 
-// LDS before the tile: match and valid masks and two sets of wave totals.
+// LDS before the tile: match and valid masks and the waves' totals.
 struct TileMasks {
     uint32_t low[kMaxWords], up[kMaxWords], valid[kMaxWords];
-    uint32_t wave[2][kWaves];
+    uint32_t wave[kWaves];
 };
 static_assert(sizeof(TileMasks) % 16 == 0, "the tile behind it is read 16 bytes at a time");
 
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void k_sparse_first(
         }
         if (!last) {
             uint32_t all;
-            int64_t slot = region + listed + block_rank(r.left, m.wave[0], all);
+            int64_t slot = region + listed + block_rank(r.left, m.wave, all);
             for (uint32_t b = r.left; b; b &= b - 1, ++slot) {
                 dst.h[slot] = static_cast<int32_t>(h0 + s4 + __ffs(static_cast<int>(b)) - 1);
                 if (seg.jobs) dst.job[slot] = job;
@@ -400,13 +400,13 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void k_sparse_list(SegSrc seg,
         const uint32_t o = __shfl_up(run, d);
         if (lane >= d) run += o;
     }
-    if (lane == 63) m.wave[0][wave] = run;
+    if (lane == 63) m.wave[wave] = run;
     __syncthreads();
     uint32_t total = 0;
     run -= extent;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-        const uint32_t t = m.wave[0][w];
+        const uint32_t t = m.wave[w];
         run += w < wave ? t : 0u;
         total += t;
     }
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(kThreads, kMinWaves) void k_sparse_list(SegSrc seg,
             uint16_t* s_list = reinterpret_cast<uint16_t*>(tile);
             uint32_t all;
             const int64_t base = region + listed;
-            uint32_t rank = block_rank(r.left, m.wave[0], all);
+            uint32_t rank = block_rank(r.left, m.wave, all);
             for (uint32_t b = r.left; b; b &= b - 1, ++rank) {
                 const int s = 4 * tid + __ffs(static_cast<int>(b)) - 1;
                 const uint32_t from = s_slot[s];

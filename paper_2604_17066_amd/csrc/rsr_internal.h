@@ -586,6 +586,5 @@ rsr_status boundary_callback(rsr_ctx* ctx, const rsr_system* sys, const uint32_t
                              uint8_t* d_side);
 hipError_t launch_sample_jobs(hipStream_t st, int n, int K, const JobDev* jobs,
                               const int64_t* offsets, int n_jobs, int64_t total, int grid_cap);
-hipError_t launch_copy_u64(hipStream_t st, const uint64_t* src, uint64_t* dst, int count);
 
 }  // namespace rsr
