@@ -916,8 +916,7 @@ rsr_status rsr_classify(rsr_ctx* ctx, const rsr_refs* refs, const uint32_t* d_sa
         cb.match[1] = reinterpret_cast<uint32_t*>(ctx->ws.casc_index + 3 * stride);
         cb.stride = stride;
         cb.set_counters(ctx->ws.casc_counters);
-        if (form == RSR_AUTO && refs->sparse &&
-            rsr::sparse_label_pays(refs->n * (refs->K - 1), n_max, N)) {
+        if (form == RSR_AUTO && refs->sparse && rsr::sparse_label_pays(refs, N)) {
             RSR_HIP(ctx, rsr::launch_dom_sparse(ctx->stream, refs,
                                                 rsr::single_src(d_samples, N, d_flags, nullptr),
                                                 rsr::JobTiles(), cb, ctx->cu_count));

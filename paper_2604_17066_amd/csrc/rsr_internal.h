@@ -291,14 +291,19 @@ __device__ __forceinline__ uint8_t* seg_Y(const SegSrc& s, int j) {
 constexpr int kSparseSmallBits = 384;
 inline double sparse_density(int bits, int64_t rows);
 
-// Whether it is on such rows, the longer side `rows`: with few of them the
-// transposes of many samples take longer than the cascade's one round of plain
-// tests.  1e6 samples, paths and cuts of networks, sparse / cascade in us: 20 bits
-// and up to 16 rows 11 / 8.5; 120 bits 4 rows 11.5 / 8.9, 8 rows 12.2 / 9.3, 16
-// rows 12.3 / 11.9, 20 rows 12.3 / 27.8; 590 bits 4 rows 27 / 22, 16 rows 28 / 33.
-// 1e4 samples: 7.5 / 9.4 with 20 bits, 8 / 12 with 16 rows of 295.
-inline bool sparse_label_pays(int bits, int64_t rows, int64_t N) {
-    return N < int64_t{1} << 17 || rows > (bits <= 64 ? 16 : 8);
+// Whether it is on such rows and N samples: with at most 16 rows a side the
+// transposes may take longer than the cascade's one round of plain tests, and a
+// tile's few slices leave most waves of its block idle, so that wide rows wait
+// for one.  Sparse / cascade in us, paths and cuts of networks: 1e6 samples, 20
+// bits 11 / 8.5, 120 bits 4 rows 11.5 / 8.9, 8 rows 12.2 / 9.3, 16 rows 12.3 /
+// 11.9, 20 rows 12.3 / 27.8, 590 bits 4 rows 27 / 22, 16 rows 28 / 33; 1e5
+// samples, 60 bits 8.8 / 7.5; 1e4 samples, 20 bits 7.5 / 9.4, 295 bits 16 rows
+// 8 / 12.  Rows of 300 set bits, 1000 samples: 4 rows 15.5 / 9.5, 16 rows 17 / 13.
+inline bool sparse_label_pays(const rsr_refs* refs, int64_t N) {
+    const int64_t rows = refs->R_L > refs->R_U ? refs->R_L : refs->R_U;
+    if (rows > 16) return true;
+    if (N >= int64_t{1} << 15 && (rows <= 8 || refs->n * (refs->K - 1) <= 64)) return false;
+    return refs->chunks <= 32;  // of one slice a side
 }
 
 // The same for counting every match, where a sample does not stop at its first

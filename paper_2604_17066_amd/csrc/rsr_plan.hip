@@ -557,8 +557,7 @@ rsr_status rsr_plan_create(rsr_ctx* ctx, const rsr_job* jobs, int32_t n_jobs,
     std::vector<int64_t>& host_offsets = p->offsets;
     int64_t max_total = 0, max_words = 0, max_grad = 0;
     for (Segment& s : p->segs) {
-        if (s.refs->consistent && s.refs->sparse &&
-            rsr::sparse_label_pays(s.n * (s.K - 1), std::max(s.refs->R_L, s.refs->R_U), s.total))
+        if (s.refs->consistent && s.refs->sparse && rsr::sparse_label_pays(s.refs, s.total))
             s.choice = kSparse;
         if (s.total > 0x7FFFFFFFll) {
             free_plan(p);
