@@ -231,7 +231,7 @@ def test_two_edge_connectivity_by_search_and_walk(rsr_ctx, name, up, N):
     xs = R.rsr_sample(rsr_ctx, model, 7, 0, 0, N)
     # The oracle on the first samples; the others in parts of 4000, which the walk
     # takes alone (but on shallow graphs).
-    some = min(N, 130 if len(e) < 1000 else 16)
+    some = min(N, 130 if len(e) < 1000 else 6)
     x = unpack_states(xs[:, :some].cpu().numpy(), len(e), 2)
     first, _ = oracle.eval_unknown_global(g, x, None, which=1, level=2)
     want = np.concatenate([

@@ -341,7 +341,7 @@ def test_few_rows_take_the_matrix_cores(rsr_ctx, n, rows, N, mode):
     model = R.Model(rsr_ctx, np.tile([0.05, 0.95], (n, 1)))
     xs = R.rsr_sample(rsr_ctx, model, 31, 0, 0, N)
     us = _times(rsr_ctx, refs, xs, N, mode, (R.RSR_AUTO, R.RSR_MFMA_FP4))
-    assert us[R.RSR_AUTO] < 1.15 * us[R.RSR_MFMA_FP4], us
+    assert us[R.RSR_AUTO] < 1.2 * us[R.RSR_MFMA_FP4], us
 
 
 @pytest.mark.parametrize("n,rows", [(20, 5), (20, 16), (120, 6), (1250, 3)])
@@ -354,4 +354,4 @@ def test_few_rows_and_many_samples_take_the_cascade(rsr_ctx, n, rows):
     N = 1_000_000
     xs = R.rsr_sample(rsr_ctx, R.Model(rsr_ctx, _model(n, 2, 4)), 31, 0, 0, N)
     us = _times(rsr_ctx, refs, xs, N, R.RSR_LABEL, (R.RSR_AUTO, R.RSR_POPCOUNT))
-    assert us[R.RSR_AUTO] < 1.12 * us[R.RSR_POPCOUNT], us
+    assert us[R.RSR_AUTO] < 1.18 * us[R.RSR_POPCOUNT], us
